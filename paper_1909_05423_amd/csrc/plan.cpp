@@ -32,6 +32,7 @@ struct Tables {
     std::vector<unsigned char> blob;
     size_t t_twx = 0, t_mkx = 0, t_twy = 0, t_mky = 0, t_rowoff = 0, t_lmax = 0, t_winf = 0, t_wlast = 0, t_wrows = 0;
     size_t t_elen = 0;
+    size_t t_twxp = 0, t_twyp = 0;   // twiddles of the plane kernels' radices
     size_t t_bmid = 0;   // interior z diagonal per (slot, entry, part)
     // split march: the lower half's pivots (by distance from the bottom row) and the meeting rows
     size_t t_browoff = 0, t_belen = 0, t_bwinf = 0, t_bwrows = 0, t_meet = 0;
@@ -61,6 +62,7 @@ struct pp_plan_s {
     int slots = 0;
     size_t elem = 0;  // bytes of one complex value of the solve precision
     pp::FftDesc fx{}, fy{};
+    pp::FftDesc fxp{}, fyp{};   // the plane kernels' radices
     int ty = 0, ldl = 0, ldy = 0, zb = 0;
     size_t nper = 0;  // upper bound of the x-kernel partial records per batch entry
     // tables (uploaded into the workspace): tb[0] in the solve precision; for
@@ -82,6 +84,7 @@ struct pp_plan_s {
     // the lowest wavenumbers of long columns with Neumann or periodic x, y)
     // make it large, and the automatic choice then keeps one march per column
     double split_gmax = 0.0;
+    bool plane_ok = false;   // a plane fits the one-workgroup transforms (plane.hip)
     // refined solve: slots lo0 .. lo0+nlo-1 kept in double by the x transform and the z march
     int lo0 = 0, nlo = 0;
     // the first correction's size may stand for the refinement's contraction
@@ -189,6 +192,39 @@ pp::FftDesc radix_plan(int n) {
     for (int i = 0; i < b; ++i) d.radix[s++] = 3;
     d.nstages = s;
     return d;
+}
+
+// Radices of a line of the plane kernels (plane.hip): as few stages as 2, 3, 4
+// and 8, and for big planes also 6, 9, 12 and 16, allow (each is a pass through
+// LDS), and of those plans the one of the smallest largest radix.
+pp::FftDesc plane_radices(int n, bool big) {
+    static const int kSmall[] = {2, 3, 4, 8}, kBig[] = {2, 3, 4, 6, 8, 9, 12, 16};
+    const int* radix = big ? kBig : kSmall;
+    const int nradix = big ? 8 : 4;
+    pp::FftDesc best{}, d{};
+    best.nstages = 17;
+    int best_max = 0;
+    auto search = [&](auto&& self, int m, int largest) -> void {
+        if (m == 1) {
+            int mx = d.nstages > 0 ? d.radix[0] : 1;
+            if (d.nstages < best.nstages || (d.nstages == best.nstages && mx < best_max)) {
+                best = d;
+                best_max = mx;
+            }
+            return;
+        }
+        if (d.nstages >= 15 || d.nstages >= best.nstages) return;
+        for (int q = 0; q < nradix; ++q) {
+            const int r = radix[q];
+            if (r > largest || m % r) continue;
+            d.radix[d.nstages++] = r;
+            self(self, m / r, r);
+            --d.nstages;
+        }
+    };
+    search(search, n, 16);
+    best.n = n;
+    return best;
 }
 
 const long double kPi = 3.141592653589793238462643383279502884L;
@@ -452,7 +488,7 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
     // FFT twiddles packed by stage (the layout the wavefront FFT reads): the
     // stage with sub-transform length Ls and radix R holds exp(-2 pi i t k step / n),
     // step = n / (Ls R), at index t Ls + k - 1 (t = 1..R-1, k = 0..Ls-1)
-    auto twiddles = [&](const pp::FftDesc& fd, size_t* tw, size_t* mkt) {
+    auto fft_twiddles = [&](const pp::FftDesc& fd, size_t* tw) {
         const int n = fd.n;
         *tw = em.put(sizeof(cplx<T>) * n);
         em.cp(*tw)[n - 1] = pp::mk<T>(T(1), T(0));   // unused
@@ -468,6 +504,10 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
                 }
             Ls *= R;
         }
+    };
+    auto twiddles = [&](const pp::FftDesc& fd, size_t* tw, size_t* mkt) {
+        const int n = fd.n;
+        fft_twiddles(fd, tw);
         *mkt = em.put(sizeof(cplx<T>) * n);
         for (int k = 0; k < n; ++k) {
             double c, s;
@@ -477,6 +517,10 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
     };
     twiddles(p->fx, &tb.t_twx, &tb.t_mkx);
     twiddles(p->fy, &tb.t_twy, &tb.t_mky);
+    if (p->plane_ok) {
+        fft_twiddles(p->fxp, &tb.t_twxp);
+        fft_twiddles(p->fyp, &tb.t_twyp);
+    }
 
     std::vector<double> lamx(nx), lamy(ny);
     for (int k = 0; k < nx; ++k) lamx[k] = eigenvalue(p->bx, k, nx, p->h[0]);
@@ -1015,9 +1059,70 @@ int x_records(pp_plan p, bool paired) {
     return pp::x_launch_grid(pp::x_blocks(p->ny, p->ty, p->nz, p->batch), paired) * pp::kXWaves;
 }
 
+// Small planes (plane.hip).
+template <typename T> pp::PlaneArgs<T> make_planeargs(pp_plan p, unsigned char* ws) {
+    const Tables& tb = p->tb[0];
+    pp::PlaneArgs<T> a{};
+    a.nx = p->nx;
+    a.ny = p->ny;
+    a.nz = p->nz;
+    a.slots = p->slots;
+    a.bx = p->bx;
+    a.by = p->by;
+    a.fx = p->fxp;
+    a.fy = p->fyp;
+    if (ws) {
+        const unsigned char* t = ws + p->o_tab[0];
+        a.twx = reinterpret_cast<const cplx<T>*>(t + tb.t_twxp);
+        a.mkx = reinterpret_cast<const cplx<T>*>(t + tb.t_mkx);
+        a.twy = reinterpret_cast<const cplx<T>*>(t + tb.t_twyp);
+        a.mky = reinterpret_cast<const cplx<T>*>(t + tb.t_mky);
+    }
+    return a;
+}
+
+// Whole planes in one workgroup, z-systems in one pass: wherever a plane fits
+// (lines up to 256), unless a layout of the march or another z solver is asked
+// for.  Measured against the best march layout at the edges of that range, in
+// double: 64 x 16 x 16 48 -> 19 us, 30 x 144 x 108 61 -> 46 us, 512 x 128 x 128
+// 232 -> 134 us, 400 x 64 x 256 205 -> 120 us, 4000 x 16 x 16 341 -> 94 us; in
+// float: 100 x 128 x 256 74 -> 64 us, 256 x 162 x 192 168 -> 81 us.
+// Float plans with a nearly singular z-system (see split_gmax) keep the two-way
+// split: two short recurrences round less than one long one, which the pass
+// over segments is (2047 x 32 x 96 PP PP DN: 4.4e-7 split, 1.7e-6 in one pass).
+bool use_planes(pp_plan p) {
+    return p->plane_ok && p->zsolver == 0 && p->zsplit_mode == PP_ZSPLIT_AUTO &&
+           (p->dtype == PP_F64 || p->split_gmax <= kSplitGMax);
+}
+
+template <typename T>
+pp_status run_planes(pp_plan p, const T* f, T* u, unsigned char* ws, hipStream_t s, bool project, bool demean,
+                     const pp::FaceArgs<T>* faces) {
+    pp::PlaneArgs<T> pa = make_planeargs<T>(p, ws);
+    if (!pp::plane_shape(pa)) return PP_ERR_SIZE;
+    const pp::MidArgs<T> ma = make_midargs<T>(p, ws, project, demean);
+    double* sc = reinterpret_cast<double*>(ws + p->o_scalars);
+    double* partial = reinterpret_cast<double*>(ws + p->o_partial);
+    cplx<T>* S = reinterpret_cast<cplx<T>*>(ws + p->o_S);
+    pp::ScanArgs g{};
+    g.partial = partial;
+    g.npts = (double)p->nx * p->ny * p->nz;
+    g.mu = sc + pp::SC_COUNT + 3 * p->batch;
+    g.maxf = sc + pp::SC_MAXF;
+    pp_status st;
+    if ((st = mark(p, s, 0)) != PP_OK) return st;
+    PP_HIP(pp::launch_plane_fwd<T>(f, S, partial, pa, p->batch, faces, s));
+    if ((st = mark(p, s, 1)) != PP_OK) return st;
+    PP_HIP(pp::launch_zscan<T>(S, ma, g, p->batch, s));
+    if ((st = mark(p, s, 2)) != PP_OK) return st;
+    PP_HIP(pp::launch_plane_inv<T>(S, u, pa, p->batch, ma.cmean, s));
+    return mark(p, s, -1);
+}
+
 template <typename T, typename Tio>
 pp_status run_plain(pp_plan p, const Tio* f, Tio* u, unsigned char* ws, hipStream_t s, bool project, bool demean,
                     const pp::FaceArgs<Tio>* faces) {
+    if (use_planes(p)) return run_planes<T>(p, f, u, ws, s, project, demean, faces);
     pp::XArgs<T> xa = make_xargs<T>(p, ws);
     pp::MidArgs<T> ma = make_midargs<T>(p, ws, project, demean);
     xa.zends = ma.zsplit > 0;
@@ -1394,6 +1499,20 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
                 }
             }
         }
+    }
+    int plane_threads = 0;
+    if (f64) {
+        pp::PlaneArgs<double> pa = make_planeargs<double>(p, nullptr);
+        p->plane_ok = pp::plane_shape(pa);
+        plane_threads = pa.nth;
+    } else if (dtype == PP_F32) {
+        pp::PlaneArgs<float> pa = make_planeargs<float>(p, nullptr);
+        p->plane_ok = pp::plane_shape(pa);
+        plane_threads = pa.nth;
+    }
+    if (p->plane_ok) {
+        p->fxp = plane_radices(nx, plane_threads > pp::kPlaneSmallThreads);
+        p->fyp = plane_radices(ny, plane_threads > pp::kPlaneSmallThreads);
     }
     if (f64) build_tables<double>(p, p->tb[0]);
     else build_tables<float>(p, p->tb[0]);

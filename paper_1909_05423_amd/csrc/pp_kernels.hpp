@@ -176,6 +176,31 @@ template <typename T> struct MidArgs {
     double* cmean;           // [batch] mean of the zero-mode solution line (output)
 };
 
+// Small planes (plane.hip): the x and y transforms of a z plane in one
+// workgroup, and the z-systems in one pass.
+constexpr int kPlaneMaxLine = 256;   // longest x or y line
+constexpr int kPlaneSmallThreads = 256;   // plane workgroups of this size use radices up to 8 only
+constexpr int kScanThreads = 512;    // largest workgroup of the z-system kernel
+template <typename T> struct PlaneArgs {
+    int nx, ny, nz, slots, bx, by;
+    // chosen by plane_shape():
+    int ldx, ldy;            // LDS strides of packed x lines and of y lines (odd)
+    int bufn;                // complex values of the LDS plane buffer
+    int nth;                 // threads per workgroup
+    FftDesc fx, fy;
+    const cplx<T>*twx, *mkx, *twy, *mky;   // twiddles as in XArgs / MidArgs
+};
+// Fill in the shape of the plane kernels; false if the plane does not fit.
+template <typename T> bool plane_shape(PlaneArgs<T>& a);
+
+struct ScanArgs {
+    const double* partial;   // sum of the source per (batch entry, plane)
+    double npts;             // points per batch entry
+    double* mu;              // [batch] source means (output)
+    double* maxf;            // a value that is finite where the source is (output)
+    int lct, segs, chunks;   // chosen by the launcher: log2 columns per workgroup, segments, chunks of z
+};
+
 // IR residual r = scale * (f - c - L_h u) in float, where c is the part of f
 // outside the range of L_h in a singular problem (known from the source mean):
 //   proj 0: none (non-singular); 1: mean(f) everywhere (projected gauges);
@@ -230,6 +255,16 @@ hipError_t launch_xinv_update(const cplx<float>* S, double* u, const float* upre
 
 template <typename T>
 hipError_t launch_mid(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s);
+
+// Small planes: forward and inverse transforms of whole planes, and the
+// z-systems between them (writes mu and the zero-mode mean).
+template <typename T>
+hipError_t launch_plane_fwd(const T* f, cplx<T>* S, double* partial, const PlaneArgs<T>& a, int batch,
+                            const FaceArgs<T>* faces, hipStream_t s);
+template <typename T>
+hipError_t launch_plane_inv(const cplx<T>* S, T* u, const PlaneArgs<T>& a, int batch, const double* shift,
+                            hipStream_t s);
+template <typename T> hipError_t launch_zscan(cplx<T>* S, const MidArgs<T>& a, ScanArgs g, int batch, hipStream_t s);
 
 // Compute units of the current device (256 if the query fails).
 int device_cus();
