@@ -30,7 +30,7 @@ using pp::cplx;
 // Host tables of one precision and their byte offsets inside the blob.
 struct Tables {
     std::vector<unsigned char> blob;
-    size_t t_twx = 0, t_mkx = 0, t_twy = 0, t_mky = 0, t_rowoff = 0, t_lmax = 0, t_winf = 0, t_wlast = 0, t_wrows = 0;
+    size_t t_twx = 0, t_mkx = 0, t_twy = 0, t_mky = 0, t_rowoff = 0, t_winf = 0, t_wlast = 0, t_wrows = 0;
     size_t t_elen = 0;
     size_t t_twxp = 0, t_twyp = 0;   // twiddles of the plane kernels' radices
     size_t t_bmid = 0;   // interior z diagonal per (slot, entry, part)
@@ -63,7 +63,7 @@ struct pp_plan_s {
     size_t elem = 0;  // bytes of one complex value of the solve precision
     pp::FftDesc fx{}, fy{};
     pp::FftDesc fxp{}, fyp{};   // the plane kernels' radices
-    int ty = 0, ldl = 0, ldy = 0, zb = 0;
+    int ty = 0, ldl = 0, ldy = 0;
     size_t nper = 0;  // upper bound of the x-kernel partial records per batch entry
     // tables (uploaded into the workspace): tb[0] in the solve precision; for
     // PP_F32_REFINED also tb[1] in double (the double-arithmetic x transform and
@@ -611,8 +611,6 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
     tb.table_rows = rows;
     tb.t_rowoff = em.put(sizeof(int) * slots);
     std::memcpy(tb.blob.data() + tb.t_rowoff, rowoff.data(), sizeof(int) * slots);
-    tb.t_lmax = em.put(sizeof(int) * slots);
-    std::memcpy(tb.blob.data() + tb.t_lmax, lmax.data(), sizeof(int) * slots);
     // per-entry lengths: a lane reads its table row only while its entry's
     // pivots still change, so slots with a few slowly converging entries (the
     // smallest wavenumbers) do not read whole rows for most of z
@@ -913,7 +911,6 @@ pp::MidArgs<T> make_midargs(pp_plan p, unsigned char* ws, bool project, bool dem
     a.bx = p->bx;
     a.by = p->by;
     a.ldy = p->ldy;
-    a.zb = p->zb;
     spectral_strides(p, &a.sstride, &a.zstride);
     a.singular = p->singular ? 1 : 0;
     a.project = project ? 1 : 0;
@@ -925,7 +922,6 @@ pp::MidArgs<T> make_midargs(pp_plan p, unsigned char* ws, bool project, bool dem
     a.twy = reinterpret_cast<const cplx<T>*>(t + tb.t_twy);
     a.mky = reinterpret_cast<const cplx<T>*>(t + tb.t_mky);
     a.rowoff = reinterpret_cast<const int*>(t + tb.t_rowoff);
-    a.lmax = reinterpret_cast<const int*>(t + tb.t_lmax);
     a.elen = reinterpret_cast<const int*>(t + tb.t_elen);
     a.wrows = reinterpret_cast<const cplx<T>*>(t + tb.t_wrows);
     a.winf = reinterpret_cast<const cplx<T>*>(t + tb.t_winf);
@@ -1056,7 +1052,7 @@ pp_status collect(pp_plan p) {
 // (<= p->nper, which sizes the partial region of the workspace); paired: the
 // inverse kernel with float spectra, which runs half the workgroups.
 int x_records(pp_plan p, bool paired) {
-    return pp::x_launch_grid(pp::x_blocks(p->ny, p->ty, p->nz, p->batch), paired) * pp::kXWaves;
+    return pp::x_launch_grid(pp::x_blocks(p->ny, p->ty, p->nz, p->batch), paired) * pp::kXGroups * pp::xdir_waves(p->nx);
 }
 
 // Small planes (plane.hip).
@@ -1404,7 +1400,7 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
     if ((code[4] == pp::BC_P) != (code[5] == pp::BC_P)) return PP_ERR_BC;   // periodic z needs both faces
     if (code[4] == pp::BC_P && nz < 3) return PP_ERR_SIZE;                     // Sherman-Morrison splitting
     if (!factor23(nx) || !factor23(ny)) return PP_ERR_SIZE;
-    if (nx > pp::kMaxLine || ny > pp::kMaxLine || ny > pp::kZThreads * pp::kZOwned) return PP_ERR_SIZE;
+    if (nx > pp::kMaxLine || ny > pp::kMaxLine) return PP_ERR_SIZE;
     if ((long long)nz * batch > 65535) return PP_ERR_SIZE;
 
     pp_plan p = new (std::nothrow) pp_plan_s;
@@ -1433,48 +1429,39 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
     p->fy = radix_plan(ny);
     p->ldl = pp::padded_len(nx);
     p->ldy = pp::padded_len(ny);
-    // row pairs (lines) per x workgroup: each wavefront transforms lpw whole lines
-    // (64 * rmax >= lpw * nx values); capped by the rows present
+    // row pairs (lines) per x workgroup: each group of wavefronts transforms lpw
+    // whole lines (64 waves kXVals >= lpw * nx values); capped by the rows present
     int lines;
     {
-        const int epl = (nx + 63) / 64;
-        // (rows of 256: one line per wavefront, the exact-count form with four values per lane)
-        const int lpw = (nx == 256) ? 1 : std::max(1, pp::xdir_rmax(nx) / epl);
-        lines = std::min(pp::kXWaves * lpw, (ny + 1) / 2);
-        // the inverse gathers slots * lines (slot, row pair) values, rmax/2 per thread
-        while (lines > 1 && (size_t)((nx + 1) / 2) * lines > (size_t)pp::kXThreads * (pp::xdir_rmax(nx) / 2)) --lines;
-        // LDS: the lines plus two twiddle tables of nx; fewer lines to keep two
-        // workgroups per CU, and a single line may use the whole LDS
-        // (the refined solve's forward x transform works in double)
+        const int lw = 64 * pp::xdir_waves(nx);
+        const int epl = (nx + lw - 1) / lw;
+        // (rows of 256: one line per wavefront, the exact-count form with four
+        // values per lane; lines shared by wavefronts: one per group)
+        const int lpw = (nx == 256 || lw > 64) ? 1 : std::max(1, pp::kXVals / epl);
+        lines = std::min(pp::kXGroups * lpw, (ny + 1) / 2);
+        // the inverse gathers slots * lines (slot, row pair) values, kXVals/2 per thread
+        while (lines > 1 && (size_t)((nx + 1) / 2) * lines > (size_t)pp::xdir_threads(nx) * (pp::kXVals / 2)) --lines;
+        // LDS: the lines plus the twiddle tables (the second, of the DCT, with
+        // Neumann or Dirichlet rows); fewer lines to keep two workgroups per CU
+        // (the refined solve's forward x transform works in double).  Lines
+        // shared by wavefronts bring enough of them in one workgroup and keep
+        // four lines (eight rows: whole 128-byte lines of double spectra) where
+        // the LDS allows.
         const size_t xelem = (dtype == PP_F32) ? sizeof(cplx<float>) : sizeof(cplx<double>);
-        auto xlds = [&](int l) { return ((size_t)l * pp::padded_len(nx) + 2 * (size_t)nx) * xelem; };
-        const int lines_all = lines;
-        while (lines > 1 && xlds(lines) > (size_t)pp::kXLdsBytes) --lines;
-        // except for the exact-count shape (one line of 64 rmax values per
-        // wavefront, kXWaves lines): kept at one workgroup per CU when its LDS
-        // allows (double rows of 1024), since the general form is slower still
-        if (lines_all == pp::kXWaves && lpw == 1 && nx == 64 * pp::xdir_rmax(nx) && xlds(lines_all) <= (size_t)pp::kXLdsMax)
-            lines = lines_all;
+        const size_t tables = p->bx == pp::BC_P ? 1 : 2;
+        auto xlds = [&](int l) { return ((size_t)l * pp::padded_len(nx) + tables * (size_t)nx) * xelem; };
+        const size_t target = lw > 64 ? (size_t)pp::kXLdsMax : (size_t)pp::kXLdsBytes;
+        while (lines > 1 && xlds(lines) > target) --lines;
         if (xlds(lines) > (size_t)pp::kXLdsMax) lines = 0;
     }
-    // z planes per chunk: each wavefront of the z march transforms whole planes,
-    // ppw = rmax / ceil(ny/64) of them per chunk; the LDS holds the chunk and the twiddles
-    {
-        const int nw = pp::kZThreads / 64;
-        const int epl = (ny + 63) / 64;
-        const int ppw = pp::zmarch_rmax(ny) / epl;
-        const int ldy = pp::padded_len(ny);
-        const int zb_lds = (int)((pp::kZLdsBytes / p->elem - (size_t)ny) / (size_t)ldy);
-        p->zb = std::min({nw * ppw, nz, zb_lds});
-    }
-    if (lines < 1 || p->zb < 1) {
+    if (lines < 1) {
         delete p;
         return PP_ERR_SIZE;
     }
     p->ty = 2 * lines;
     // partial records per batch entry: one per (workgroup, wavefront) of the persistent
     // x kernels, whose grid never exceeds the row blocks of all batch entries
-    p->nper = (size_t)((ny + p->ty - 1) / p->ty) * nz * batch * pp::kXWaves;
+    p->nper = (size_t)((ny + p->ty - 1) / p->ty) * nz * batch * pp::kXGroups * pp::xdir_waves(nx);
     // split march: the meeting point on a chunk boundary near the middle (the
     // refined solve's march has the float march's chunks)
     {

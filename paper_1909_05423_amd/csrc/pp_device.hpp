@@ -215,17 +215,25 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // t * Ls + k - 1, so the stages occupy [Ls - 1, R Ls - 1) one after another
 // (N - 1 entries in all) and the lanes of a stage, which run over consecutive
 // k, read consecutive entries (no LDS bank conflicts).
-template <int R, int MAXB, bool INV, typename T>
-__device__ __forceinline__ void wfft_stage(cplx<T>* line, int N, int Ls, const cplx<T>* tw, int lane) {
+//
+// LW > 64: LW / 64 wavefronts share the line, `lane` counting through them; the
+// reads and writes of a stage are then separated by workgroup barriers, which
+// every thread of the workgroup must reach (`active` false: no line of its own).
+template <int LW> __device__ __forceinline__ void line_sync() {
+    if constexpr (LW == 64) wave_lds_sync();
+    else lds_barrier();
+}
+template <int R, int MAXB, bool INV, int LW, typename T>
+__device__ __forceinline__ void wfft_stage(cplx<T>* line, int N, int Ls, const cplx<T>* tw, int lane, bool active) {
     const int nbf = N / R;
     const float inv_ls = 1.0f / (float)Ls;
     cplx<T> v[MAXB][R];
     int dst[MAXB];
 #pragma unroll
     for (int i = 0; i < MAXB; ++i) {
-        const int j = lane + 64 * i;
+        const int j = lane + LW * i;
         dst[i] = -1;
-        if (j < nbf) {
+        if (active && j < nbf) {
             const int k = j - fdiv(j, inv_ls) * Ls;
 #pragma unroll
             for (int t = 0; t < R; ++t) v[i][t] = line[pad(j + t * nbf)];
@@ -240,7 +248,7 @@ __device__ __forceinline__ void wfft_stage(cplx<T>* line, int N, int Ls, const c
             dst[i] = (j - k) * R + k;
         }
     }
-    wave_lds_sync();
+    line_sync<LW>();
 #pragma unroll
     for (int i = 0; i < MAXB; ++i) {
         if (dst[i] >= 0) {
@@ -248,19 +256,24 @@ __device__ __forceinline__ void wfft_stage(cplx<T>* line, int N, int Ls, const c
             for (int t = 0; t < R; ++t) line[pad(dst[i] + t * Ls)] = v[i][t];
         }
     }
-    wave_lds_sync();
+    line_sync<LW>();
 }
 
-// One line of d.n <= 64 * EPL complex values, transformed by one wavefront.
-template <int EPL, bool INV, typename T>
-__device__ __forceinline__ void wfft(cplx<T>* line, const FftDesc& d, const cplx<T>* tw, int lane) {
+// One line of d.n <= LW * EPL complex values, transformed by LW / 64 wavefronts.
+// RECOMP: the LDS addresses of a stage are formed anew in every stage.  Without
+// it the compiler keeps those of all four radices in registers across the
+// stages, which is right only for kernels with registers to spare.
+template <int EPL, bool INV, typename T, bool RECOMP = false, int LW = 64>
+__device__ __forceinline__ void wfft(cplx<T>* line, const FftDesc& d, const cplx<T>* tw, int lane,
+                                     bool active = true) {
     int Ls = 1;
     for (int s = 0; s < d.nstages; ++s) {
         const int R = d.radix[s];
-        if (R == 8) wfft_stage<8, cdiv(EPL, 8), INV, T>(line, d.n, Ls, tw, lane);
-        else if (R == 4) wfft_stage<4, cdiv(EPL, 4), INV, T>(line, d.n, Ls, tw, lane);
-        else if (R == 3) wfft_stage<3, cdiv(EPL, 3), INV, T>(line, d.n, Ls, tw, lane);
-        else wfft_stage<2, cdiv(EPL, 2), INV, T>(line, d.n, Ls, tw, lane);
+        if constexpr (RECOMP) asm volatile("" : "+v"(lane));
+        if (R == 8) wfft_stage<8, cdiv(EPL, 8), INV, LW, T>(line, d.n, Ls, tw, lane, active);
+        else if (R == 4) wfft_stage<4, cdiv(EPL, 4), INV, LW, T>(line, d.n, Ls, tw, lane, active);
+        else if (R == 3) wfft_stage<3, cdiv(EPL, 3), INV, LW, T>(line, d.n, Ls, tw, lane, active);
+        else wfft_stage<2, cdiv(EPL, 2), INV, LW, T>(line, d.n, Ls, tw, lane, active);
         Ls *= R;
     }
 }

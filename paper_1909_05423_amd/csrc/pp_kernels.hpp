@@ -17,34 +17,24 @@ enum Bc : int { BC_P = 0, BC_N = 1, BC_D = 2 };
 // butterfly, two radix-4, three radix-3 or four radix-2 butterflies per thread
 // in registers).
 constexpr int kEpt = 8;
-constexpr int kXThreads = 256;                 // x kernels: lines of nx per workgroup = kXElems / nx
-constexpr int kXElems = kXThreads * kEpt;
-constexpr int kXBlocksPerCU = 2;               // persistent x-kernel workgroups per CU (all resident)
-constexpr int kXWaves = kXThreads / 64;
+// x kernels: kXGroups lines at a time, each by xdir_waves(nx) wavefronts.
+// One wavefront transforms a line of up to 512; longer lines are shared by two
+// (to 1024) or four, so that a lane holds at most 8 values of a line whatever
+// its length (16 and 32 per lane left one wavefront per SIMD, and spilled).
+constexpr int kXGroups = 4;
+constexpr int xdir_waves(int nx) { return nx <= 512 ? 1 : (nx <= 1024 ? 2 : 4); }
+constexpr int xdir_threads(int nx) { return 64 * kXGroups * xdir_waves(nx); }
+constexpr int kXBlocksPerCU = 2;               // persistent x-kernel workgroups per CU
 constexpr int kXLdsBytes = 96 * 1024;          // x-kernel LDS target (lines + twiddle tables), two workgroups per CU
 constexpr int kXLdsMax = 160 * 1024 - 1024;    // x-kernel LDS ceiling (one workgroup per CU)
-// x-kernel register shape: values per lane of one line (64 * RMAX >= nx).
-constexpr int xdir_rmax(int nx) { return nx <= 512 ? 8 : (nx <= 1024 ? 16 : 32); }
-constexpr int kZThreads = 512;                 // z march: planes per chunk = kZElems / ny
-constexpr int kZElems = kZThreads * kEpt;
-// Entries (spectral y positions) one thread of the z march owns: ny <= kZThreads * kZOwned;
-// a chunk holds zb <= kEpt / ceil(ny / kZThreads) planes.
-constexpr int kZOwned = 4;
+constexpr int kXVals = kEpt;                   // values per lane of one line (64 xdir_waves(nx) kXVals >= nx)
 constexpr int kMaxLine = 2048;                 // longest x or y line
-// z-march LDS budget: zb padded lines plus ny twiddles.
-constexpr int kZLdsBytes = 160 * 1024 - 1024;
-constexpr size_t zmarch_lds_bytes(int zb, int ldy, int ny, size_t elem) {
-    return ((size_t)zb * ldy + (size_t)ny) * elem;
-}
-// z-march register shape: values per lane of a chunk (64 * RMAX >= ny).
-constexpr int zmarch_rmax(int ny) { return ny <= 512 ? 8 : (ny <= 1024 ? 16 : 32); }
-
 // x-direction kernels: a workgroup owns `ty` consecutive rows (y0 .. y0+ty-1)
 // of one z plane of one batch entry, packed two rows per complex line.
 template <typename T> struct XArgs {
     int nx, ny, nz, slots;   // slots = ceil(nx/2) spectral columns per row
     int bx;                  // boundary type along x (Bc)
-    int ty;                  // rows per workgroup (even; ty/2 * nx <= kXElems)
+    int ty;                  // rows per workgroup (even)
     int ldl;                 // LDS line stride (padded_len(nx))
     long sstride, zstride;   // spectral array: element (b, m, z, y) at b*slots*nz*ny + m*sstride + z*zstride + y
     FftDesc fx;              // radix plan for nx
@@ -116,7 +106,6 @@ template <typename T> struct MidArgs {
     int ny, nz, slots;
     int bx, by;
     int ldy;                 // LDS line stride (padded_len(ny))
-    int zb;                  // z planes per LDS chunk (zb * ny <= kZElems, zb * own <= kEpt)
     int singular;            // zero mode present (slot 0, entry 0, real part)
     int project;             // subtract the source mean from the zero-mode line
     int demean;              // report the mean of the zero-mode solution (subtracted by the x inverse)
@@ -127,8 +116,7 @@ template <typename T> struct MidArgs {
     const cplx<T>* twy;      // FFT twiddles of length ny, packed by stage (wfft_stage)
     const cplx<T>* mky;      // exp(-i pi k / (2 ny))
     const int* rowoff;       // per slot: first table row
-    const int* lmax;         // per slot: rows stored (z < lmax reads the table)
-    const int* elen;         // per (slot, entry): rows in which this entry's pivots differ from winf (<= lmax)
+    const int* elen;         // per (slot, entry): rows in which this entry's pivots differ from winf
     const cplx<T>* wrows;    // [row][ny] (w_re, w_im) reciprocal pivots
     const cplx<T>* winf;     // [slot][ny] converged reciprocal pivot
     const cplx<T>* wlast;    // [slot][ny] reciprocal pivot of the last row

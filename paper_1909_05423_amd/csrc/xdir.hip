@@ -98,8 +98,8 @@ template <typename T> __device__ __forceinline__ void put_spec(cplx<T>* p, const
 // Forward x kernel, persistent: each workgroup walks row blocks in the order
 // of x_first_block / x_next_block; the rows of the next block are in
 // flight into registers while the current one is transformed.  Each wavefront
-// transforms its own lines (line j = wave + NW p holds rows 2j, 2j+1; its lanes
-// hold columns n = lane + 64 k) without workgroup barriers; the transposed
+// transforms its own lines (line j = wave + NG p holds rows 2j, 2j+1; its lanes
+// hold columns n = lane + LW k) without workgroup barriers; the transposed
 // write of the spectral columns reads across lines.  Partial sums of the source
 // (sum, max |f|) are written per wavefront.
 //
@@ -116,9 +116,11 @@ template <typename T> __device__ __forceinline__ void put_spec(cplx<T>* p, const
 // on rows of 1024, spill under it (the float one 104 registers, 3.0 ms at
 // 1024 x 1024 x 512; unconstrained it takes AGPRs instead, one wave per SIMD,
 // 1.75 ms).  The general form of the fused residual (RES) spills under it too.
-template <typename T, typename Tin, int RMAX, bool FACES, bool FULL = true, bool RES = false>
+// Lines shared by wavefronts: the workgroup's own wavefronts per SIMD.
+template <typename T, typename Tin, int WPL, int RMAX, bool FACES, bool FULL = true, bool RES = false>
 constexpr int kXfwdMinWaves =
-    (RES && !FULL) ? 1
+    WPL > 1 ? WPL
+    : (RES && !FULL) ? 1
                    : ((sizeof(T) == 4 && sizeof(Tin) == 4 && RMAX <= 8) || (sizeof(T) == 8 && RMAX == 8 && !FACES)) ? 2
                                                                                                                      : 1;
 
@@ -128,18 +130,19 @@ constexpr int kXfwdMinWaves =
 // from the adjacent lanes (exact-count form) or from loads (general form).
 // Neighbours past a face are read at a valid address (the periodic image, or
 // the cell itself with the sign of the ghost rule) as in k_residual.
-template <typename T, typename Tin, typename Ts, int NTH, int RMAX, bool FULL, bool FACES, bool RES = false>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWaves<T, Tin, RMAX, FACES, FULL, RES>))) void k_xfwd(const Tin* __restrict__ f, cplx<Ts>* __restrict__ S,
+template <typename T, typename Tin, typename Ts, int WPL, int RMAX, bool FULL, bool FACES, bool RES = false>
+__global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_per_eu(kXfwdMinWaves<T, Tin, WPL, RMAX, FACES, FULL, RES>))) void k_xfwd(const Tin* __restrict__ f, cplx<Ts>* __restrict__ S,
                                               double* __restrict__ partial, XArgs<T> a, int nblocks,
                                               FaceArgs<Tin> fa) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool SPLIT = !std::is_same_v<T, Ts>;   // double arithmetic, float spectra + double slots
-    constexpr int NW = NTH / 64;
+    constexpr int NTH = 64 * kXGroups * WPL, LW = 64 * WPL, NG = kXGroups;   // lanes per line; lines at a time
+    constexpr bool RECOMP = !FULL || WPL > 1;   // (see wfft)
     constexpr int PAIRS = RMAX / 2;   // FULL: column writes per thread, slots * nlines == NTH * PAIRS
-    const int nx = FULL ? 64 * RMAX : a.nx;
-    const int ny = a.ny, nz = a.nz, ty = FULL ? 2 * NW : a.ty, ldl = a.ldl;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nx = FULL ? LW * RMAX : a.nx;
+    const int ny = a.ny, nz = a.nz, ty = FULL ? 2 * NG : a.ty, ldl = a.ldl;
+    const int tid = threadIdx.x, lane = tid & (LW - 1);        // lane: within the group of wavefronts sharing a line
+    const int wave = __builtin_amdgcn_readfirstlane(tid / LW);   // the group
     const int nlines = ty >> 1;
     const int nyb = (ny + ty - 1) / ty;
     cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
@@ -147,19 +150,19 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
     cplx<T>* mkl = twl + nx;
     for (int i = tid; i < nx; i += NTH) {
         twl[i] = a.twx[i];
-        mkl[i] = a.mkx[i];
+        if (a.bx != BC_P) mkl[i] = a.mkx[i];
     }
-    const int epl = FULL ? RMAX : (nx + 63) >> 6;
+    const int epl = FULL ? RMAX : (nx + LW - 1) / LW;
     const float inv_epl = 1.0f / (float)epl, inv_nl = 1.0f / (float)nlines;
     // periodic rows of 512, double spectra: the transform's first stage runs
     // on the row registers (w512_first; in float the extra registers cost more
     // occupancy than the LDS round trip saves)
     // (not with the fused residual, whose neighbour values need the registers,
     // nor with the split store, which spilled with it)
-    constexpr bool R512 = FULL && RMAX == 8 && sizeof(T) == 8 && !RES && !SPLIT;
+    constexpr bool R512 = FULL && WPL == 1 && RMAX == 8 && sizeof(T) == 8 && !RES && !SPLIT;
     const bool reg512 = R512 && a.bx == BC_P;
 
-    // register r: line j = wave + NW * (r / epl), column n = lane + 64 * (r % epl)
+    // register r: line j = wave + NG * (r / epl), column n = lane + LW * (r % epl)
     Tin ra[RMAX], rb[RMAX];
     // RES: u0 at the two rows (ua, ub), at the row below a and above b (uya, uyb)
     // and at the planes below and above (uza0, uza1, uzb0, uzb1)
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) {
             const int p = FULL ? 0 : fdiv(r, inv_epl);
-            const int j = wave + NW * p, n = lane + 64 * (r - p * epl);
+            const int j = wave + NG * p, n = lane + LW * (r - p * epl);
             const int ya = xb.y0 + 2 * j;
             if (FULL) {
                 ra[r] = ld_stream(src + (size_t)ya * nx + n);
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
 #pragma unroll
             for (int r = 0; r < RMAX; ++r) {
                 const int p = FULL ? 0 : fdiv(r, inv_epl);
-                const int j = wave + NW * p, n = lane + 64 * (r - p * epl);
+                const int j = wave + NG * p, n = lane + LW * (r - p * epl);
                 const int ya = xb.y0 + 2 * j;
                 const bool va = FULL || (j < nlines && n < nx && ya < ny);
                 const bool vb = FULL || (j < nlines && n < nx && ya + 1 < ny);
@@ -263,7 +266,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
             const float t1 = rot1(c[r], dir);
             const float t2 = rot1(c[rw], dir);
             const bool wrap = dir < 0 ? (lane == 0) : (lane == 63);
-            const int n = lane + 64 * r;
+            const int n = lane + LW * r;
             const bool face = dir < 0 ? (n == 0) : (n == nx - 1);
             const int kind = a.fbc[dir < 0 ? 0 : 1];
             if (face && kind != BC_P) return (kind == BC_D ? -1.0 : 1.0) * (double)c[r];
@@ -274,10 +277,13 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
     };
     // per-wavefront sums of the source, one record per (batch entry, workgroup, wavefront)
     const int batch = (int)(nblocks / ((size_t)nyb * nz));
+    constexpr int NW = NTH / 64;
+    const int wid = tid >> 6;
+    const bool lead = (tid & 63) == 0;
     const size_t rec_per_batch = (size_t)gridDim.x * NW;
-    if (lane == 0) {
+    if (lead) {
         for (int bb = 0; bb < batch; ++bb) {
-            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NW + wave;
+            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NW + wid;
             partial[2 * rec] = 0.0;
             partial[2 * rec + 1] = 0.0;
         }
@@ -289,8 +295,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
     if constexpr (RES) rscale = a.sc[SC_SCALE];
     auto flush = [&]() {
         const double s_ = wave_sum(acc) * rscale, m_ = wave_max(amax) * rscale;
-        if (lane == 0 && cur_b >= 0) {
-            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NW + wave;
+        if (lead && cur_b >= 0) {
+            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NW + wid;
             partial[2 * rec] = s_;
             partial[2 * rec + 1] = m_;
         }
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) {
             const int p = FULL ? 0 : fdiv(r, inv_epl);
-            const int j = wave + NW * p, n = lane + 64 * (r - p * epl);
+            const int j = wave + NG * p, n = lane + LW * (r - p * epl);
             if (FULL || (j < nlines && n < nx)) {
                 double la = 0.0, lb = 0.0;   // x-face lift of rows ya, ya + 1 at column n (FULL)
                 if constexpr (FACES && FULL) {
@@ -416,7 +422,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
                 if (ya == 0 || ya + 1 == ny - 1 || xb.z == 0 || xb.z == nz - 1) {
 #pragma unroll
                     for (int r = 0; r < RMAX; ++r) {
-                        const int n = lane + 64 * r;
+                        const int n = lane + LW * r;
                         const double la = face_lift_yz(fa, xb.b, n, ya, xb.z, nx, ny, nz);
                         const double lb = face_lift_yz(fa, xb.b, n, ya + 1, xb.z, nx, ny, nz);
                         const double fa_ = (double)vf[r].x - la, fb_ = (double)vf[r].y - lb;
@@ -432,7 +438,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
             for (int r = 0; r < RMAX; ++r) {
                 if (reg512) break;
                 const int p = FULL ? 0 : fdiv(r, inv_epl);
-                const int j = wave + NW * p, n = lane + 64 * (r - p * epl);
+                const int j = wave + NG * p, n = lane + LW * (r - p * epl);
                 const int ya = xb.y0 + 2 * j;
                 const bool edge = FULL ? (ya == 0 || ya + 1 == ny - 1 || xb.z == 0 || xb.z == nz - 1)
                                        : (j < nlines && n < nx);
@@ -475,13 +481,13 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
 #pragma unroll
                 for (int t = 0; t < 8; ++t) line[pad(lane + 64 * t)] = vf[t];
             }
-        } else if (FULL) {
-            wave_lds_sync();
-            wfft<RMAX, false, T>(lds + wave * ldl, a.fx, twl, lane);
+        } else if (FULL || WPL > 1) {
+            line_sync<LW>();
+            wfft<RMAX, false, T, RECOMP, LW>(lds + wave * ldl, a.fx, twl, lane, FULL || wave < nlines);
         } else {
-            for (int j = wave; j < nlines; j += NW) {
+            for (int j = wave; j < nlines; j += NG) {
                 wave_lds_sync();
-                wfft<RMAX, false, T>(lds + j * ldl, a.fx, twl, lane);
+                wfft<RMAX, false, T, RECOMP>(lds + j * ldl, a.fx, twl, lane);
             }
         }
         lds_barrier();
@@ -547,8 +553,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(kXfwdMinWav
 // write per-wavefront partials (sum over the gauge region, max |d|, max |u|).
 // Tp: type of the previous solution an update adds to (Tout: u itself, in
 // place; float: the separate array uprev holding the first float solution).
-template <typename T, typename Tout, typename Tp, int NTH, int MODE, int RMAX, bool FULL>
-__global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tout* __restrict__ u,
+template <typename T, typename Tout, typename Tp, int WPL, int MODE, int RMAX, bool FULL>
+__global__ __launch_bounds__(64 * kXGroups * WPL) void k_xinv(const cplx<T>* __restrict__ S, Tout* __restrict__ u,
                                               const Tp* __restrict__ uprev, XArgs<T> a,
                                               const double* __restrict__ shift, const double* __restrict__ scalars,
                                               int gauge_region, double* __restrict__ partial, int nblocks) {
@@ -556,14 +562,15 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
     constexpr bool INPLACE = std::is_same_v<Tp, Tout>;
     // rows of 512, double spectra: w512_* stages when x is periodic (in float
     // the extra registers cost more occupancy than the LDS round trip saves)
-    constexpr bool R512 = FULL && RMAX == 8 && sizeof(T) == 8;
+    constexpr bool R512 = FULL && WPL == 1 && RMAX == 8 && sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int NW = NTH / 64;
+    constexpr int NTH = 64 * kXGroups * WPL, LW = 64 * WPL, NG = kXGroups;   // lanes per line; lines at a time
+    constexpr bool RECOMP = !FULL || WPL > 1;   // (see wfft)
     constexpr int PAIRS = RMAX / 2;    // (slot, row pair) gathers per thread: slots * nlines <= NTH * PAIRS
-    const int nx = FULL ? 64 * RMAX : a.nx;
-    const int ny = a.ny, nz = a.nz, ty = FULL ? 2 * NW : a.ty, ldl = a.ldl;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nx = FULL ? LW * RMAX : a.nx;
+    const int ny = a.ny, nz = a.nz, ty = FULL ? 2 * NG : a.ty, ldl = a.ldl;
+    const int tid = threadIdx.x, lane = tid & (LW - 1);        // lane: within the group of wavefronts sharing a line
+    const int wave = __builtin_amdgcn_readfirstlane(tid / LW);   // the group
     const int nlines = ty >> 1;
     const int nyb = (ny + ty - 1) / ty;
     cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
@@ -571,7 +578,7 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
     cplx<T>* mkl = twl + nx;
     for (int i = tid; i < nx; i += NTH) {
         twl[i] = a.twx[i];
-        mkl[i] = a.mkx[i];
+        if (a.bx != BC_P) mkl[i] = a.mkx[i];
     }
     const float inv_nl = 1.0f / (float)nlines;
     const int npair = a.slots * nlines;
@@ -581,10 +588,13 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
     if (UPD) inv_scale = scalars[SC_INVSCALE];
 
     // refinement partials, one record per (batch entry, workgroup, wavefront)
+    constexpr int NW = NTH / 64;
+    const int wid = tid >> 6;
+    const bool lead = (tid & 63) == 0;
     const size_t rec_per_batch = (size_t)gridDim.x * NW;
-    if (UPD && lane == 0) {
+    if (UPD && lead) {
         for (int bb = 0; bb < batch; ++bb) {
-            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NW + wave;
+            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NW + wid;
             partial[3 * rec] = 0.0;
             partial[3 * rec + 1] = 0.0;
             partial[3 * rec + 2] = 0.0;
@@ -599,8 +609,8 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
         if (!UPD) return;
         if (chk != chk) dmax = chk;
         const double s_ = wave_sum(acc), d_ = wave_max(dmax), u_ = wave_max(umax);
-        if (lane == 0 && cur_b >= 0) {
-            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NW + wave;
+        if (lead && cur_b >= 0) {
+            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NW + wid;
             partial[3 * rec] = s_;
             partial[3 * rec + 1] = d_;
             partial[3 * rec + 2] = u_;
@@ -681,7 +691,7 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
             for (int k = 0; k < RMAX; ++k)
 #pragma unroll
                 for (int part = 0; part < 2; ++part)
-                    uo[2 * k + part] = (double)prv[(size_t)(xb.y0 + 2 * wave + part) * nx + lane + 64 * k];
+                    uo[2 * k + part] = (double)prv[(size_t)(xb.y0 + 2 * wave + part) * nx + lane + LW * k];
         }
         // the next block's spectra (past the end: this block's again, unused)
         const int nxt = x_next_block<sizeof(T) == 4>(blk);   // pairs in float (x_next_block)
@@ -692,10 +702,13 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
         double gshift = 0.0;
         if (UPD) gshift = scalars[SC_COUNT + 2 * batch + xb.b];
         // 2. per own line (FULL: exactly one): inverse pre-processing, inverse FFT, row writes
-        for (int j = wave; FULL ? j == wave : j < nlines; j += NW) {
+        // (lines shared by wavefronts: one per group, and groups without one
+        // pass through for the barriers)
+        for (int j = wave; (FULL || WPL > 1) ? j == wave : j < nlines; j += NG) {
             cplx<T>* line = lds + j * ldl;
-            if (a.bx != BC_P) {
-                for (int k = lane; k < half; k += 64) {
+            const bool mine = FULL || WPL == 1 || j < nlines;
+            if (a.bx != BC_P && mine) {
+                for (int k = lane; k < half; k += LW) {
                     if (k == 0) continue;                       // W_0 = X_0
                     const cplx<T> xk = line[pad(k)];
                     if (2 * k == nx) {
@@ -708,7 +721,7 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
                     }
                 }
             }
-            wave_lds_sync();
+            line_sync<LW>();
             // periodic rows of 512: the last stage's outputs stay in registers,
             // in the order the row writes take them (see w512_last)
             cplx<T> vl[R512 ? 8 : 1];
@@ -719,15 +732,15 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
                     w512_second<true, T>(line, tw, lane);
                     w512_last<true, T>(line, tw, lane, vl);
                 } else {
-                    wfft<RMAX, true, T>(line, a.fx, twl, lane);
+                    wfft<RMAX, true, T, RECOMP, LW>(line, a.fx, twl, lane, mine);
                 }
             } else {
-                wfft<RMAX, true, T>(line, a.fx, twl, lane);
+                wfft<RMAX, true, T, RECOMP, LW>(line, a.fx, twl, lane, mine);
             }
             if (FULL) {
 #pragma unroll
                 for (int k = 0; k < RMAX; ++k) {
-                    const int n = lane + 64 * k;
+                    const int n = lane + LW * k;
                     int pos = n;
                     if (a.bx != BC_P) pos = makhoul_pos(n, nx);
                     cplx<T> c;
@@ -755,8 +768,8 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
                         }
                     }
                 }
-            } else {
-                for (int n = lane; n < nx; n += 64) {
+            } else if (mine) {
+                for (int n = lane; n < nx; n += LW) {
                     int pos = n;
                     if (a.bx != BC_P) pos = makhoul_pos(n, nx);
                     cplx<T> c = line[pad(pos)];
@@ -795,7 +808,7 @@ __global__ __launch_bounds__(NTH) void k_xinv(const cplx<T>* __restrict__ S, Tou
 }
 
 template <typename T> static size_t x_lds_bytes(const XArgs<T>& a) {
-    return ((size_t)(a.ty >> 1) * a.ldl + 2 * (size_t)a.nx) * sizeof(cplx<T>);
+    return ((size_t)(a.ty >> 1) * a.ldl + (a.bx == BC_P ? 1 : 2) * (size_t)a.nx) * sizeof(cplx<T>);
 }
 
 hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
@@ -836,31 +849,32 @@ int x_blocks(int ny, int ty, int nz, int batch) { return ((ny + ty - 1) / ty) * 
 
 int x_launch_grid(int nblocks, bool paired) { return x_grid(paired ? (nblocks + 1) / 2 : nblocks); }
 
-// Row blocks of the FULL shape: nx = 64 RMAX, one line per wavefront, whole blocks
-// in y.  Lines of 2048 never fit four to a workgroup, so RMAX = 32 has no FULL form.
-template <int RMAX, typename T> static bool x_full(const XArgs<T>& a) {
-    return RMAX <= 16 && a.nx == 64 * RMAX && a.ty == 2 * kXWaves && a.ny % a.ty == 0;
+// Row blocks of the FULL shape: nx = 64 WPL RMAX, one line per group of
+// wavefronts, whole blocks in y.  (None for four wavefronts per line: at 1024
+// threads its prefetched rows spill, the general form does not.)
+template <int WPL, int RMAX, typename T> static bool x_full(const XArgs<T>& a) {
+    return a.nx == 64 * WPL * RMAX && a.ty == 2 * kXGroups && a.ny % a.ty == 0;
 }
 
-template <typename T, typename Tin, typename Ts, int RMAX, bool FACES, bool RES = false>
+template <typename T, typename Tin, typename Ts, int WPL, int RMAX, bool FACES, bool RES = false>
 static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
                                     const FaceArgs<Tin>& fa, hipStream_t s) {
     const int nb = x_blocks(a.ny, a.ty, a.nz, batch);
-    if constexpr (RMAX <= 16) {
-        if (x_full<RMAX>(a)) {
-            const hipError_t le = allow_lds<k_xfwd<T, Tin, Ts, kXThreads, RMAX, true, FACES, RES>>();
+    if constexpr (WPL <= 2) {
+        if (x_full<WPL, RMAX>(a)) {
+            const hipError_t le = allow_lds<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>();
             if (le != hipSuccess) return le;
-            hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, kXThreads, RMAX, true, FACES, RES>),
-                               dim3(x_launch_grid(nb, false)), dim3(kXThreads), x_lds_bytes(a), s, f, S, partial, a,
+            hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>),
+                               dim3(x_launch_grid(nb, false)), dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, f, S, partial, a,
                                nb, fa);
             return hipGetLastError();
         }
     }
     {
-        const hipError_t le = allow_lds<k_xfwd<T, Tin, Ts, kXThreads, RMAX, false, FACES, RES>>();
+        const hipError_t le = allow_lds<k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>>();
         if (le != hipSuccess) return le;
-        hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, kXThreads, RMAX, false, FACES, RES>), dim3(x_launch_grid(nb, false)),
-                           dim3(kXThreads), x_lds_bytes(a), s, f, S, partial, a, nb, fa);
+        hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>), dim3(x_launch_grid(nb, false)),
+                           dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, f, S, partial, a, nb, fa);
     }
     return hipGetLastError();
 }
@@ -872,25 +886,26 @@ hipError_t launch_xfwd_res(const double* f, cplx<float>* S, double* partial, con
     if (a.nx > 512) return hipErrorInvalidValue;
     const FaceArgs<double> none{};
     if (faces) {
-        if (a.nx == 256) return launch_xfwd_shape<double, double, float, 4, true, true>(f, S, partial, a, batch, *faces, s);
-        if (a.nx == 384) return launch_xfwd_shape<double, double, float, 6, true, true>(f, S, partial, a, batch, *faces, s);
-        return launch_xfwd_shape<double, double, float, 8, true, true>(f, S, partial, a, batch, *faces, s);
+        if (a.nx == 256) return launch_xfwd_shape<double, double, float, 1, 4, true, true>(f, S, partial, a, batch, *faces, s);
+        if (a.nx == 384) return launch_xfwd_shape<double, double, float, 1, 6, true, true>(f, S, partial, a, batch, *faces, s);
+        return launch_xfwd_shape<double, double, float, 1, 8, true, true>(f, S, partial, a, batch, *faces, s);
     }
-    if (a.nx == 256) return launch_xfwd_shape<double, double, float, 4, false, true>(f, S, partial, a, batch, none, s);
-    if (a.nx == 384) return launch_xfwd_shape<double, double, float, 6, false, true>(f, S, partial, a, batch, none, s);
-    return launch_xfwd_shape<double, double, float, 8, false, true>(f, S, partial, a, batch, none, s);
+    if (a.nx == 256) return launch_xfwd_shape<double, double, float, 1, 4, false, true>(f, S, partial, a, batch, none, s);
+    if (a.nx == 384) return launch_xfwd_shape<double, double, float, 1, 6, false, true>(f, S, partial, a, batch, none, s);
+    return launch_xfwd_shape<double, double, float, 1, 8, false, true>(f, S, partial, a, batch, none, s);
 }
 
 template <typename T, typename Tin, typename Ts, bool FACES>
 static hipError_t launch_xfwd_any(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
                                   const FaceArgs<Tin>& fa, hipStream_t s) {
-    // rows of 256 = 64 x 4 and 384 = 64 x 6: exact-count forms with four and
-    // six values per lane
-    if (a.nx == 256) return launch_xfwd_shape<T, Tin, Ts, 4, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx == 384) return launch_xfwd_shape<T, Tin, Ts, 6, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx <= 512) return launch_xfwd_shape<T, Tin, Ts, 8, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx <= 1024) return launch_xfwd_shape<T, Tin, Ts, 16, FACES>(f, S, partial, a, batch, fa, s);
-    return launch_xfwd_shape<T, Tin, Ts, 32, FACES>(f, S, partial, a, batch, fa, s);
+    // exact-count forms: rows of 256 = 64 x 4, 384 = 64 x 6, 512 = 64 x 8, 768 =
+    // 128 x 6, 1024 = 128 x 8
+    if (a.nx == 256) return launch_xfwd_shape<T, Tin, Ts, 1, 4, FACES>(f, S, partial, a, batch, fa, s);
+    if (a.nx == 384) return launch_xfwd_shape<T, Tin, Ts, 1, 6, FACES>(f, S, partial, a, batch, fa, s);
+    if (a.nx <= 512) return launch_xfwd_shape<T, Tin, Ts, 1, 8, FACES>(f, S, partial, a, batch, fa, s);
+    if (a.nx == 768) return launch_xfwd_shape<T, Tin, Ts, 2, 6, FACES>(f, S, partial, a, batch, fa, s);
+    if (a.nx <= 1024) return launch_xfwd_shape<T, Tin, Ts, 2, 8, FACES>(f, S, partial, a, batch, fa, s);
+    return launch_xfwd_shape<T, Tin, Ts, 4, 8, FACES>(f, S, partial, a, batch, fa, s);
 }
 
 template <typename T, typename Tin, typename Ts>
@@ -901,26 +916,26 @@ hipError_t launch_xfwd(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T
     return launch_xfwd_any<T, Tin, Ts, false>(f, S, partial, a, batch, none, s);
 }
 
-template <typename T, typename Tout, typename Tp, int MODE, int RMAX>
+template <typename T, typename Tout, typename Tp, int MODE, int WPL, int RMAX>
 static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, const XArgs<T>& a, int batch,
                                     const double* shift, const double* scalars, int gauge_region, double* partial,
                                     hipStream_t s) {
     const int nb = x_blocks(a.ny, a.ty, a.nz, batch);
-    if constexpr (RMAX <= 16) {
-        if (x_full<RMAX>(a)) {
-            const hipError_t le = allow_lds<k_xinv<T, Tout, Tp, kXThreads, MODE, RMAX, true>>();
+    if constexpr (WPL <= 2) {
+        if (x_full<WPL, RMAX>(a)) {
+            const hipError_t le = allow_lds<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>();
             if (le != hipSuccess) return le;
-            hipLaunchKernelGGL((k_xinv<T, Tout, Tp, kXThreads, MODE, RMAX, true>),
-                               dim3(x_launch_grid(nb, sizeof(T) == 4)), dim3(kXThreads), x_lds_bytes(a), s, S, u,
+            hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>),
+                               dim3(x_launch_grid(nb, sizeof(T) == 4)), dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, S, u,
                                uprev, a, shift, scalars, gauge_region, partial, nb);
             return hipGetLastError();
         }
     }
     {
-        const hipError_t le = allow_lds<k_xinv<T, Tout, Tp, kXThreads, MODE, RMAX, false>>();
+        const hipError_t le = allow_lds<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>>();
         if (le != hipSuccess) return le;
-        hipLaunchKernelGGL((k_xinv<T, Tout, Tp, kXThreads, MODE, RMAX, false>),
-                           dim3(x_launch_grid(nb, sizeof(T) == 4)), dim3(kXThreads), x_lds_bytes(a), s, S, u, uprev,
+        hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>),
+                           dim3(x_launch_grid(nb, sizeof(T) == 4)), dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, S, u, uprev,
                            a, shift, scalars, gauge_region, partial, nb);
     }
     return hipGetLastError();
@@ -930,16 +945,18 @@ template <typename T, typename Tout, typename Tp, int MODE>
 static hipError_t launch_xinv_any(const cplx<T>* S, Tout* u, const Tp* uprev, const XArgs<T>& a, int batch,
                                   const double* shift, const double* scalars, int gauge_region, double* partial,
                                   hipStream_t s) {
-    if (a.nx == 256)   // 64 x 4: exact-count form with four values per lane
-        return launch_xinv_shape<T, Tout, Tp, MODE, 4>(S, u, uprev, a, batch, shift, scalars, gauge_region, partial, s);
-    if (a.nx == 384)   // 64 x 6: exact-count form with six values per lane
-        return launch_xinv_shape<T, Tout, Tp, MODE, 6>(S, u, uprev, a, batch, shift, scalars, gauge_region, partial, s);
-    if (a.nx <= 512)
-        return launch_xinv_shape<T, Tout, Tp, MODE, 8>(S, u, uprev, a, batch, shift, scalars, gauge_region, partial, s);
-    if (a.nx <= 1024)
-        return launch_xinv_shape<T, Tout, Tp, MODE, 16>(S, u, uprev, a, batch, shift, scalars, gauge_region, partial,
-                                                        s);
-    return launch_xinv_shape<T, Tout, Tp, MODE, 32>(S, u, uprev, a, batch, shift, scalars, gauge_region, partial, s);
+    // exact-count forms as in launch_xfwd_any
+    auto go = [&](auto wpl, auto rmax) {
+        return launch_xinv_shape<T, Tout, Tp, MODE, decltype(wpl)::value, decltype(rmax)::value>(
+            S, u, uprev, a, batch, shift, scalars, gauge_region, partial, s);
+    };
+    using std::integral_constant;
+    if (a.nx == 256) return go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    if (a.nx == 384) return go(integral_constant<int, 1>{}, integral_constant<int, 6>{});
+    if (a.nx <= 512) return go(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+    if (a.nx == 768) return go(integral_constant<int, 2>{}, integral_constant<int, 6>{});
+    if (a.nx <= 1024) return go(integral_constant<int, 2>{}, integral_constant<int, 8>{});
+    return go(integral_constant<int, 4>{}, integral_constant<int, 8>{});
 }
 
 template <typename T, typename Tout>

@@ -1,7 +1,7 @@
 // The z-march: y transforms fused with the tridiagonal solves along z.
 //
 // One workgroup owns one spectral x column (slot m) of one batch entry: the
-// ny x nz block S[b][m][:, :].  It marches z upward in chunks of zb planes:
+// ny x nz block S[b][m][:, :].  It marches z upward in chunks of planes:
 //   load chunk -> forward y transform of every plane (LDS FFT + post-process)
 //   -> forward elimination of the Thomas algorithm for every (entry, part)
 //   -> store the eliminated right-hand sides in place;
@@ -35,295 +35,19 @@
 
 namespace pp {
 
-// Per-lane share of a chunk: a wavefront owns planes wave, wave + NW, ...; its
-// lanes hold elements y = lane + 64 k of each.  Register r of a lane covers
-// plane p = r / epl and element k = r % epl of that plane (epl = ceil(ny/64)).
-struct LaneSlot {
-    int l, y;
-};
-__device__ __forceinline__ LaneSlot lane_slot(int r, int epl, float inv_epl, int wave, int nw, int lane) {
-    const int p = fdiv(r, inv_epl);
-    LaneSlot s;
-    s.l = wave + nw * p;
-    s.y = lane + 64 * (r - p * epl);
-    return s;
-}
-
-// Planes whose pivots and right-hand sides are fetched ahead of each stretch of
-// the (serial) z recurrences.
-constexpr int kZBatch = 4;
-
-// Tabulated reciprocal pivot of plane z for entry e (converged / last-row values come from registers).
-template <typename T>
-__device__ __forceinline__ cplx<T> row_pivot(const MidArgs<T>& a, int lmax, int roff, int z, int e, cplx<T> winf,
-                                             cplx<T> wlast) {
-    if (z == a.nz - 1) return wlast;
-    if (z < lmax) return a.wrows[(size_t)(roff + z) * a.ny + e];
-    return winf;
-}
-
-// The z march.  RMAX: chunk values per lane (64 * RMAX >= ny); OWN: y entries per
-// thread in the z recurrences (NTH * OWN >= ny).
-template <typename T, int NTH, int RMAX, int OWN>
-__global__ __launch_bounds__(NTH) void k_zmarch(cplx<T>* __restrict__ S, MidArgs<T> a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int NW = NTH / 64;
-    const int m = blockIdx.x, b = blockIdx.y;
-    const int ny = a.ny, nz = a.nz, ldy = a.ldy, zb = a.zb;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // LDS: zb planes of ny (padded), then the y twiddles
-    cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
-    cplx<T>* twl = lds + zb * ldy;
-    for (int i = tid; i < ny; i += NTH) twl[i] = a.twy[i];
-    cplx<T>* col = S + (size_t)b * a.slots * nz * ny + (size_t)m * a.sstride;
-    const size_t zs = (size_t)a.zstride;
-    const bool pairslot = (a.bx != BC_P) || (m == 0);
-    const bool sep = (a.by == BC_P) && pairslot;
-    const bool sing = a.singular && (m == 0);
-    const int lmax = a.lmax[m], roff = a.rowoff[m];
-    const T scale = a.scale;
-    const T proj = (sing && a.project) ? (T)(a.hz2 * a.mu[b]) : T(0);
-    const int half = (ny >> 1) + 1;
-    const int nchunks = (nz + zb - 1) / zb;
-    const int epl = (ny + 63) >> 6;
-    const float inv_epl = 1.0f / (float)epl;
-    const int ppw = (zb + NW - 1) / NW;          // planes per wave per chunk (ppw * epl <= RMAX)
-
-    // owned z-recurrence entries e = tid + q * NTH; converged and last-row pivots in registers
-    cplx<T> st[OWN], winf[OWN], wlast[OWN];
-    // periodic z (Sherman-Morrison; see k_zpipe): y_0 accumulator, correction, q_{z+1}
-    cplx<T> y0[OWN], corr[OWN], qn[OWN];
-    const bool zper = a.zper != 0;
-    const int alen = zper ? a.alen[m] : 0, aoff = zper ? a.aoff[m] : 0;
-    const int qlen = zper ? a.qlen[m] : 0, qoff = zper ? a.qoff[m] : 0;
-#pragma unroll
-    for (int q = 0; q < OWN; ++q) {
-        const int e = tid + q * NTH;
-        st[q] = mk<T>(T(0), T(0));
-        winf[q] = st[q];
-        wlast[q] = st[q];
-        y0[q] = st[q];
-        corr[q] = st[q];
-        qn[q] = st[q];
-        if (zper && e < ny) qn[q] = a.qlast[(size_t)m * ny + e];
-        if (e < ny) {
-            winf[q] = a.winf[(size_t)m * ny + e];
-            wlast[q] = a.wlast[(size_t)m * ny + e];
-        }
-    }
-
-    cplx<T> pre[RMAX];
-    auto fetch = [&](int z0, int nl) {
-#pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            const LaneSlot ls = lane_slot(r, epl, inv_epl, wave, NW, lane);
-            if (r < ppw * epl && ls.l < nl && ls.y < ny) pre[r] = col[(size_t)(z0 + ls.l) * zs + ls.y];
-        }
-    };
-
-    // ------------------------------------------------------------- upward
-    fetch(0, min(zb, nz));
-    for (int c = 0; c < nchunks; ++c) {
-        const int zc = c * zb;
-        const int nl = min(zb, nz - zc);
-        // own planes: prefetched values -> LDS, pre-processed for the y transform
-#pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            const LaneSlot ls = lane_slot(r, epl, inv_epl, wave, NW, lane);
-            if (r < ppw * epl && ls.l < nl && ls.y < ny) {
-                cplx<T> v = pre[r];
-                int pos = ls.y;
-                if (a.by != BC_P) {
-                    pos = makhoul_pos(ls.y, ny);
-                    if (a.by == BC_D && (ls.y & 1)) v = mk<T>(-v.x, -v.y);
-                }
-                lds[ls.l * ldy + pad(pos)] = v;
-            }
-        }
-        if (c + 1 < nchunks) fetch(zc + zb, min(zb, nz - zc - zb));
-        if (c == 0) __syncthreads();   // twiddles
-        // forward y transform of each own plane, then its post-processing
-        for (int l = wave; l < nl; l += NW) {
-            cplx<T>* line = lds + l * ldy;
-            wave_lds_sync();
-            wfft<RMAX, false, T>(line, a.fy, twl, lane);
-            if (a.by != BC_P) {
-                // DCT-II post-twiddle over the pairs (k, ny-k)
-                for (int k = lane; k < half; k += 64) {
-                    if (k == 0) continue;
-                    const cplx<T> vk = line[pad(k)];
-                    const cplx<T> wk = a.mky[k];
-                    if (2 * k == ny) {
-                        line[pad(k)] = cscale(cadd(cmul(wk, vk), cmulc(vk, wk)), T(0.5));
-                    } else {
-                        const cplx<T> vr = line[pad(ny - k)];
-                        const cplx<T> wr = a.mky[ny - k];
-                        line[pad(k)] = cscale(cadd(cmul(wk, vk), cmulc(vr, wk)), T(0.5));
-                        line[pad(ny - k)] = cscale(cadd(cmul(wr, vr), cmulc(vk, wr)), T(0.5));
-                    }
-                }
-            } else if (sep) {
-                for (int k = lane; k < half; k += 64) {
-                    if (k == 0 || 2 * k >= ny) continue;
-                    const cplx<T> zk = line[pad(k)], zr = line[pad(ny - k)];
-                    line[pad(k)] = mk<T>(T(0.5) * (zk.x + zr.x), T(0.5) * (zk.y - zr.y));
-                    line[pad(ny - k)] = mk<T>(T(0.5) * (zk.y + zr.y), T(0.5) * (zr.x - zk.x));
-                }
-            }
-        }
-        __syncthreads();
-        // forward elimination across the chunk's planes, kZBatch planes at a time
-        // (pivots and right-hand sides fetched ahead of the dependent steps);
-        // eliminated right-hand sides go to HBM
-#pragma unroll
-        for (int q = 0; q < OWN; ++q) {
-            const int e = tid + q * NTH;
-            if (e < ny) {
-                cplx<T> prev = st[q];
-                for (int l0 = 0; l0 < nl; l0 += kZBatch) {
-                    cplx<T> w[kZBatch], d[kZBatch];
-#pragma unroll
-                    for (int j = 0; j < kZBatch; ++j) {
-                        const int l = l0 + j;
-                        if (l < nl) {
-                            w[j] = row_pivot(a, lmax, roff, zc + l, e, winf[q], wlast[q]);
-                            d[j] = cscale(lds[l * ldy + pad(e)], scale);
-                        }
-                    }
-#pragma unroll
-                    for (int j = 0; j < kZBatch; ++j) {
-                        const int l = l0 + j;
-                        if (l < nl) {
-                            cplx<T> dd = d[j];
-                            if (sing && e == 0) dd.x -= proj;
-                            if (zper && zc + l < alen) {
-                                const cplx<T> al = a.arows[(size_t)(aoff + zc + l) * ny + e];
-                                y0[q].x += al.x * dd.x;
-                                y0[q].y += al.y * dd.y;
-                            }
-                            prev = mk<T>((dd.x - prev.x) * w[j].x, (dd.y - prev.y) * w[j].y);
-                            col[(size_t)(zc + l) * zs + e] = prev;
-                        }
-                    }
-                }
-                st[q] = prev;
-            }
-        }
-        __syncthreads();
-    }
-
-    // ----------------------------------------------------------- downward
-#pragma unroll
-    for (int q = 0; q < OWN; ++q) {
-        const int e = tid + q * NTH;
-        if (zper && e < ny) {
-            // st is y_{n-1}, the last eliminated value
-            const cplx<T> ig = a.inv_gamma[(size_t)m * ny + e], id = a.inv_den[(size_t)m * ny + e];
-            corr[q] = mk<T>((y0[q].x + st[q].x * ig.x) * id.x, (y0[q].y + st[q].y * ig.y) * id.y);
-        }
-        st[q] = mk<T>(T(0), T(0));
-    }
-    double csum = 0.0;
-    fetch((nchunks - 1) * zb, nz - (nchunks - 1) * zb);
-    for (int c = nchunks - 1; c >= 0; --c) {
-        const int zc = c * zb;
-        const int nl = min(zb, nz - zc);
-#pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-            const LaneSlot ls = lane_slot(r, epl, inv_epl, wave, NW, lane);
-            if (r < ppw * epl && ls.l < nl && ls.y < ny) lds[ls.l * ldy + pad(ls.y)] = pre[r];
-        }
-        if (c > 0) fetch(zc - zb, zb);
-        __syncthreads();
-        // back substitution across the chunk's planes, kZBatch planes at a time
-#pragma unroll
-        for (int q = 0; q < OWN; ++q) {
-            const int e = tid + q * NTH;
-            if (e < ny) {
-                cplx<T> nxt = st[q];
-                for (int l1 = nl - 1; l1 >= 0; l1 -= kZBatch) {
-                    cplx<T> w[kZBatch], dp[kZBatch];
-#pragma unroll
-                    for (int j = 0; j < kZBatch; ++j) {
-                        const int l = l1 - j;
-                        if (l >= 0) {
-                            w[j] = row_pivot(a, lmax, roff, zc + l, e, winf[q], wlast[q]);
-                            dp[j] = lds[l * ldy + pad(e)];
-                        }
-                    }
-#pragma unroll
-                    for (int j = 0; j < kZBatch; ++j) {
-                        const int l = l1 - j;
-                        if (l >= 0) {
-                            nxt = mk<T>(dp[j].x - w[j].x * nxt.x, dp[j].y - w[j].y * nxt.y);
-                            cplx<T> un = nxt;
-                            if (zper) {
-                                const int z = zc + l;
-                                if (z != nz - 1) {
-                                    const cplx<T> qp = (z < qlen) ? a.qrows[(size_t)(qoff + z) * ny + e]
-                                                                  : mk<T>(T(0), T(0));
-                                    qn[q] = mk<T>(qp.x - w[j].x * qn[q].x, qp.y - w[j].y * qn[q].y);
-                                }
-                                un = mk<T>(nxt.x - corr[q].x * qn[q].x, nxt.y - corr[q].y * qn[q].y);
-                            }
-                            lds[l * ldy + pad(e)] = un;
-                            if (sing && e == 0) csum += (double)un.x;
-                        }
-                    }
-                }
-                st[q] = nxt;
-            }
-        }
-        __syncthreads();
-        // inverse y transform of each own plane, written straight to HBM
-        for (int l = wave; l < nl; l += NW) {
-            cplx<T>* line = lds + l * ldy;
-            if (a.by != BC_P) {
-                // DCT-III pre-twiddle: W_k = e^{+i pi k/2N} (X_k - i X_{N-k}), X_N = 0
-                for (int k = lane; k < half; k += 64) {
-                    if (k == 0) continue;
-                    const cplx<T> xk = line[pad(k)];
-                    if (2 * k == ny) {
-                        line[pad(k)] = cmulc(mk<T>(xk.x + xk.y, xk.y - xk.x), a.mky[k]);
-                    } else {
-                        const cplx<T> xr = line[pad(ny - k)];
-                        line[pad(k)] = cmulc(mk<T>(xk.x + xr.y, xk.y - xr.x), a.mky[k]);
-                        line[pad(ny - k)] = cmulc(mk<T>(xr.x + xk.y, xr.y - xk.x), a.mky[ny - k]);
-                    }
-                }
-            } else if (sep) {
-                for (int k = lane; k < half; k += 64) {
-                    if (k == 0 || 2 * k >= ny) continue;
-                    const cplx<T> A = line[pad(k)], B = line[pad(ny - k)];
-                    line[pad(k)] = mk<T>(A.x - B.y, A.y + B.x);        // A + i B
-                    line[pad(ny - k)] = mk<T>(A.x + B.y, B.x - A.y);   // conj(A) + i conj(B)
-                }
-            }
-            wave_lds_sync();
-            wfft<RMAX, true, T>(line, a.fy, twl, lane);
-            for (int y = lane; y < ny; y += 64) {
-                int pos = y;
-                if (a.by != BC_P) pos = makhoul_pos(y, ny);
-                cplx<T> v = line[pad(pos)];
-                if (a.by == BC_D && (y & 1)) v = mk<T>(-v.x, -v.y);
-                col[(size_t)(zc + l) * zs + y] = v;
-            }
-        }
-    }
-    if (m == 0 && tid == 0) a.cmean[b] = (sing && a.demean) ? csum / (double)nz : 0.0;
-}
-
 // ---------------------------------------------------------------------------
-// Pipelined z march for y lines of up to NYMAX = 512 (NW = 8 wavefronts), of
-// exactly 384 (float, NW = 6) or of up to 1024 (float: NW = 8; double: NW = 4, so
-// that a chunk of 1024-long double planes fits in LDS), and, segmented, of up
-// to 256 (NW = 4, several workgroups per CU): the same stages as k_zmarch,
-// arranged so that the memory traffic of one chunk overlaps the arithmetic of
-// another.
+// The march k_zpipe<T, NYMAX, NW, ..., WPP> (k_zmarch over 1024), arranged so that the memory
+// traffic of one chunk overlaps the arithmetic of another: y lines of up to
+// NYMAX = 512 (NW = 8 wavefronts), of exactly 384 (float, NW = 6) and,
+// segmented, of up to 256 (NW = 4, several workgroups per CU) with one
+// wavefront per plane (WPP = 1); longer lines with a plane shared by WPP
+// wavefronts, so that a lane holds eight values of it whatever its length.
+// (Double lines of 1024 at 16 values per lane and one wavefront per SIMD: 4.81
+// -> 4.27 ms at 512 x 1024 x 1024.  Lines over 1024 ran a general march with 32
+// values per lane, 2.5 KB of them in scratch memory, and no overlap: 7.43 ->
+// 1.24 ms at 64 x 1536 x 1152.)
 //
-// A chunk is NW planes, one per wavefront; a lane holds elements y = lane + 64 k
+// For WPP = 1, a chunk is NW planes; a lane holds elements y = lane + 64 k
 // of its wavefront's plane, and a thread owns the z recurrences of entries
 // e = tid + 64 NW o (o < OWN = NYMAX / (64 NW)).  Upward, a lane prefetches its share of
 // its wavefront's plane of the next chunk into registers while the current
@@ -355,9 +79,9 @@ __global__ __launch_bounds__(NTH) void k_zmarch(cplx<T>* __restrict__ S, MidArgs
 // float, both storing float.
 
 // LDS of one march workgroup in compute precision T.
-template <typename T, int NYMAX, int NW> struct ZpipeLds {
+template <typename T, int NYMAX, int NP> struct ZpipeLds {
     static constexpr int LDY = NYMAX + NYMAX / 8;   // work-buffer plane stride (>= padded_len(NYMAX))
-    cplx<T> work[NW * LDY];
+    cplx<T> work[NP * LDY];
     cplx<T> twl[NYMAX];
     cplx<T> mkl[NYMAX];
 };
@@ -375,15 +99,17 @@ template <typename T, int NYMAX, int NW> struct ZpipeLds {
 // and substitutes away from the meeting point.  Both halves run the same code
 // on their own rows, so the column has twice the workgroups in flight.
 template <typename Tin, typename T, typename Tf, typename Tout, int NYMAX, int NW, bool FULL, bool PERZ, bool YFWD,
-          int PH = 0>
+          int PH = 0, int WPP = 1>
 __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs, cplx<Tout>* ocol, ptrdiff_t zs,
                                            const MidArgs<T>& a, const MidArgs<Tf>& af,
-                                           ZpipeLds<Tf, NYMAX, NW>& L) {
+                                           ZpipeLds<Tf, NYMAX, NW / WPP>& L) {
     constexpr int NTH = 64 * NW;
-    constexpr int kSZ = NW;                      // planes per chunk = wavefronts per workgroup
-    constexpr int EPL = NYMAX / 64;              // plane elements per lane
+    constexpr int kSZ = NW / WPP;                // planes per chunk, each shared by WPP wavefronts
+    constexpr int LW = 64 * WPP;                 // lanes per plane
+    constexpr int EPL = NYMAX / LW;              // plane elements per lane
     constexpr int OWN = NYMAX / NTH;             // z-recurrence entries per thread
-    constexpr int LDY = ZpipeLds<Tf, NYMAX, NW>::LDY;
+    constexpr int LDY = ZpipeLds<Tf, NYMAX, kSZ>::LDY;
+    constexpr bool RECOMP = WPP > 1;             // (see wfft)
     static_assert(EPL == kSZ * OWN, "one prefetch buffer serves both directions");
     cplx<Tf>* work = L.work;
     cplx<Tf>* twl = L.twl;
@@ -412,15 +138,15 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
     }
     const cplx<T>* wrows = side ? a.bwrows : (fresh ? a.fwrows : a.wrows);
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) / WPP);   // plane of the chunk
+    const int lane = WPP == 1 ? (tid & 63) : tid - wave * LW;            // among the plane's lanes
     for (int i = tid; i < ny; i += NTH) {
         twl[i] = af.twy[i];
         mkl[i] = af.mky[i];
     }
     // periodic y on lines of 512: the transforms take their first (forward) or
     // last (inverse) stage in registers (w512_*)
-    constexpr bool R512 = FULL && NYMAX == 512;
+    constexpr bool R512 = FULL && NYMAX == 512 && WPP == 1;
     const bool reg512 = R512 && a.by == BC_P;
     // (float twiddles in registers in the whole march; the split march's
     // halves read them from LDS, to fit two workgroups per CU)
@@ -515,7 +241,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
             const cplx<Tin>* src = icol + (ptrdiff_t)min(zc + wave, nz - 1) * izs;
 #pragma unroll
             for (int k = 0; k < EPL; ++k) {
-                const int y = lane + 64 * k;
+                const int y = lane + LW * k;
                 pre[k] = cvt<T>(src[(FULL || y < ny) ? y : 0]);
             }
         } else {
@@ -578,7 +304,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
             // prefetched plane -> work plane, reordered for the forward transform
 #pragma unroll
             for (int k = 0; k < EPL; ++k) {
-                const int y = lane + 64 * k;
+                const int y = lane + LW * k;
                 if (FULL || y < ny) {
                     cplx<Tf> x = cvt<Tf>(pre[k]);
                     int pos = y;
@@ -602,18 +328,19 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
             for (int t = 0; t < EPL; ++t) line[pad(lane + 64 * t)] = v[t];
             if (sep) {
                 wave_lds_sync();
-                for (int k = lane; k < half; k += 64) {
+                for (int k = lane; k < half; k += LW) {
                     if (k == 0 || 2 * k >= ny) continue;
                     const cplx<Tf> zk = line[pad(k)], zr = line[pad(ny - k)];
                     line[pad(k)] = mk<Tf>(Tf(0.5) * (zk.x + zr.x), Tf(0.5) * (zk.y - zr.y));
                     line[pad(ny - k)] = mk<Tf>(Tf(0.5) * (zk.y + zr.y), Tf(0.5) * (zr.x - zk.x));
                 }
             }
-        } else if (own) {
-            wave_lds_sync();
-            wfft<EPL, false, Tf>(line, af.fy, twl, lane);
-            if (a.by != BC_P) {
-                for (int k = lane; k < half; k += 64) {
+        } else if (own || WPP > 1) {
+            line_sync<LW>();
+            wfft<EPL, false, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
+            if (!own) {
+            } else if (a.by != BC_P) {
+                for (int k = lane; k < half; k += LW) {
                     if (k == 0) continue;
                     const cplx<Tf> vk = line[pad(k)];
                     const cplx<Tf> wk = mkl[k];
@@ -627,7 +354,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
                     }
                 }
             } else if (sep) {
-                for (int k = lane; k < half; k += 64) {
+                for (int k = lane; k < half; k += LW) {
                     if (k == 0 || 2 * k >= ny) continue;
                     const cplx<Tf> zk = line[pad(k)], zr = line[pad(ny - k)];
                     line[pad(k)] = mk<Tf>(Tf(0.5) * (zk.x + zr.x), Tf(0.5) * (zk.y - zr.y));
@@ -821,10 +548,12 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
         load_entry(zn);
         if constexpr (!LATEPIV) load_piv(zn);
         // inverse y transform of this wave's plane, written straight to HBM
-        if (FULL || wave < nl) {
+        const bool own = FULL || wave < nl;
+        if (own || WPP > 1) {
             cplx<Tf>* line = work + wave * LDY;
-            if (a.by != BC_P) {
-                for (int k = lane; k < half; k += 64) {
+            if (!own) {
+            } else if (a.by != BC_P) {
+                for (int k = lane; k < half; k += LW) {
                     if (k == 0) continue;
                     const cplx<Tf> xk = line[pad(k)];
                     if (2 * k == ny) {
@@ -836,14 +565,14 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
                     }
                 }
             } else if (sep) {
-                for (int k = lane; k < half; k += 64) {
+                for (int k = lane; k < half; k += LW) {
                     if (k == 0 || 2 * k >= ny) continue;
                     const cplx<Tf> A = line[pad(k)], B = line[pad(ny - k)];
                     line[pad(k)] = mk<Tf>(A.x - B.y, A.y + B.x);
                     line[pad(ny - k)] = mk<Tf>(A.x + B.y, B.x - A.y);
                 }
             }
-            wave_lds_sync();
+            line_sync<LW>();
             cplx<Tout>* dst = ocol + (ptrdiff_t)(zc + wave) * zs;
             if (reg512) {
                 cplx<Tf> v[EPL];
@@ -855,11 +584,11 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
 #pragma unroll
                 for (int t = 0; t < EPL; ++t) dst[lane + 64 * t] = cvt<Tout>(v[t]);
             } else {
-                wfft<EPL, true, Tf>(line, af.fy, twl, lane);
+                wfft<EPL, true, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
 #pragma unroll
                 for (int k = 0; k < EPL; ++k) {
-                    const int y = lane + 64 * k;
-                    if (FULL || y < ny) {
+                    const int y = lane + LW * k;
+                    if (FULL || (own && y < ny)) {
                         int pos = y;
                         if (a.by != BC_P) pos = makhoul_pos(y, ny);
                         cplx<Tf> x = line[pad(pos)];
@@ -892,11 +621,19 @@ template <typename T, int NYMAX, int PH> constexpr int zpipe_min_waves() {
 }
 
 // The march in one precision, in place.
-template <typename T, int NYMAX, int NW, bool FULL, bool PERZ, int PH>
+template <typename T, int NYMAX, int NW, bool FULL, bool PERZ, int PH, int WPP = 1>
 __global__ __launch_bounds__(64 * NW, (zpipe_min_waves<T, NYMAX, PH>())) void k_zpipe(cplx<T>* __restrict__ S, MidArgs<T> a) {
-    __shared__ __align__(16) ZpipeLds<T, NYMAX, NW> L;
+    __shared__ __align__(16) ZpipeLds<T, NYMAX, NW / WPP> L;
     cplx<T>* col = S + (size_t)blockIdx.y * a.slots * a.nz * a.ny + (size_t)blockIdx.x * a.sstride;
-    zpipe_body<T, T, T, T, NYMAX, NW, FULL, PERZ, true, PH>(col, a.zstride, col, a.zstride, a, a, L);
+    zpipe_body<T, T, T, T, NYMAX, NW, FULL, PERZ, true, PH, WPP>(col, a.zstride, col, a.zstride, a, a, L);
+}
+
+// The same for y lines over 1024 (one march per column).
+template <typename T, int NYMAX, int NW, bool FULL, bool PERZ, int WPP>
+__global__ __launch_bounds__(64 * NW) void k_zmarch(cplx<T>* __restrict__ S, MidArgs<T> a) {
+    __shared__ __align__(16) ZpipeLds<T, NYMAX, NW / WPP> L;
+    cplx<T>* col = S + (size_t)blockIdx.y * a.slots * a.nz * a.ny + (size_t)blockIdx.x * a.sstride;
+    zpipe_body<T, T, T, T, NYMAX, NW, FULL, PERZ, true, 0, WPP>(col, a.zstride, col, a.zstride, a, a, L);
 }
 
 // The refined solve's march: slots lo0 .. lo0+nlo-1 (the smallest x
@@ -1064,56 +801,54 @@ template <typename T> __global__ __launch_bounds__(64) void k_zseg_reduce(MidArg
 
 // the segmented march: eliminate every segment, solve the reduced systems,
 // correct and substitute (never with periodic z)
-template <typename T, int NYMAX, int NW, bool FULL>
+template <typename T, int NYMAX, int NW, bool FULL, int WPP = 1>
 static hipError_t launch_seg(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s) {
     const dim3 block(64 * NW), grid(a.slots, batch, a.zsegs);
-    hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 3>), grid, block, 0, s, S, a);
+    hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 3, WPP>), grid, block, 0, s, S, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t nth = (size_t)batch * a.slots * a.ny;
     hipLaunchKernelGGL(k_zseg_reduce<T>, dim3((unsigned)((nth + 63) / 64)), dim3(64), 0, s, a, batch);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 4>), grid, block, 0, s, S, a);
+    hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 4, WPP>), grid, block, 0, s, S, a);
     return hipGetLastError();
 }
 
-template <typename T, int NYMAX, int NW, bool FULL>
+template <typename T, int NYMAX, int NW, bool FULL, int WPP>
 static hipError_t launch_pipe(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s) {
     const dim3 block(64 * NW);
-    if (a.zsegs > 0) return launch_seg<T, NYMAX, NW, FULL>(S, a, batch, s);
-    if (a.zsplit > 0) {   // never with periodic z
-        const dim3 grid(a.slots, batch, 2);
-        hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 1>), grid, block, 0, s, S, a);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 2>), grid, block, 0, s, S, a);
-        return hipGetLastError();
+    if constexpr (NYMAX <= 1024) {   // longer lines have one march per column only
+        if (a.zsegs > 0) return launch_seg<T, NYMAX, NW, FULL, WPP>(S, a, batch, s);
+        if (a.zsplit > 0) {   // never with periodic z
+            const dim3 grid(a.slots, batch, 2);
+            hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 1, WPP>), grid, block, 0, s, S, a);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 2, WPP>), grid, block, 0, s, S, a);
+            return hipGetLastError();
+        }
     }
     const dim3 grid(a.slots, batch);
-    if (a.zper) hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, true, 0>), grid, block, 0, s, S, a);
-    else hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 0>), grid, block, 0, s, S, a);
+    if constexpr (NYMAX > 1024) {
+        if (a.zper) hipLaunchKernelGGL((k_zmarch<T, NYMAX, NW, FULL, true, WPP>), grid, block, 0, s, S, a);
+        else hipLaunchKernelGGL((k_zmarch<T, NYMAX, NW, FULL, false, WPP>), grid, block, 0, s, S, a);
+    } else {
+        if (a.zper) hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, true, 0, WPP>), grid, block, 0, s, S, a);
+        else hipLaunchKernelGGL((k_zpipe<T, NYMAX, NW, FULL, false, 0, WPP>), grid, block, 0, s, S, a);
+    }
     return hipGetLastError();
 }
 
-template <typename T, int NYMAX, int NW>
+template <typename T, int NYMAX, int NW, int WPP = 1>
 static hipError_t launch_pipe_any(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s) {
-    if (pipe_full(a, NYMAX, NW)) return launch_pipe<T, NYMAX, NW, true>(S, a, batch, s);
-    return launch_pipe<T, NYMAX, NW, false>(S, a, batch, s);
+    if (pipe_full(a, NYMAX, NW / WPP)) return launch_pipe<T, NYMAX, NW, true, WPP>(S, a, batch, s);
+    return launch_pipe<T, NYMAX, NW, false, WPP>(S, a, batch, s);
 }
 
-template <typename T, int RMAX, int OWN>
-static hipError_t launch_mid_shape(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s) {
-    const size_t lds = zmarch_lds_bytes(a.zb, a.ldy, a.ny, sizeof(cplx<T>));
-    const hipError_t le = allow_dynamic_lds(reinterpret_cast<const void*>(k_zmarch<T, kZThreads, RMAX, OWN>), kZLdsBytes);
-    if (le != hipSuccess) return le;
-    hipLaunchKernelGGL((k_zmarch<T, kZThreads, RMAX, OWN>), dim3(a.slots, batch), dim3(kZThreads), lds, s, S, a);
-    return hipGetLastError();
-}
-
-// ny <= 1024: the pipelined march (8 wavefronts; 6 for float lines of 384, 4
-// for double lines over 512); longer lines: k_zmarch with 32 values per lane and
-// four z entries per thread (ny <= 2048).
+// Lines up to 512: a wavefront per plane (8 planes at a time; 6 for float lines
+// of 384); longer lines share a plane between wavefronts, as many planes as fit
+// in LDS (four of 1024 or 1536 in double, two of 2048; eight and four in float).
 template <typename T>
 hipError_t launch_mid(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s) {
     if (a.zsolver == 1 || a.zsolver == 2) return launch_mid_pcr<T>(S, a, batch, s, a.zsolver == 2);
@@ -1129,11 +864,15 @@ hipError_t launch_mid(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s)
         if (a.ny == 384) return launch_pipe_any<T, 384, 6>(S, a, batch, s);
     }
     if (a.ny <= 512) return launch_pipe_any<T, 512, 8>(S, a, batch, s);
-    if (a.ny <= 1024) {
-        if constexpr (sizeof(T) == 4) return launch_pipe_any<T, 1024, 8>(S, a, batch, s);
-        else return launch_pipe_any<T, 1024, 4>(S, a, batch, s);
+    if constexpr (sizeof(T) == 4) {
+        if (a.ny <= 1024) return launch_pipe_any<T, 1024, 16, 2>(S, a, batch, s);
+        if (a.ny <= 1536) return launch_pipe_any<T, 1536, 12, 3>(S, a, batch, s);
+        return launch_pipe_any<T, 2048, 16, 4>(S, a, batch, s);
+    } else {
+        if (a.ny <= 1024) return launch_pipe_any<T, 1024, 8, 2>(S, a, batch, s);
+        if (a.ny <= 1536) return launch_pipe_any<T, 1536, 12, 3>(S, a, batch, s);
+        return launch_pipe_any<T, 2048, 8, 4>(S, a, batch, s);
     }
-    return launch_mid_shape<T, 32, 4>(S, a, batch, s);
 }
 
 template <int NYMAX, int NW, bool FULL>
