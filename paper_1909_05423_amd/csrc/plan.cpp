@@ -1048,13 +1048,6 @@ pp_status collect(pp_plan p) {
         if ((call) != hipSuccess) return PP_ERR_HIP; \
     } while (0)
 
-// Partial records per batch entry written by an x kernel on this device
-// (<= p->nper, which sizes the partial region of the workspace); paired: the
-// inverse kernel with float spectra, which runs half the workgroups.
-int x_records(pp_plan p, bool paired) {
-    return pp::x_launch_grid(pp::x_blocks(p->ny, p->ty, p->nz, p->batch), paired) * pp::kXGroups * pp::xdir_waves(p->nx);
-}
-
 // Small planes (plane.hip).
 template <typename T> pp::PlaneArgs<T> make_planeargs(pp_plan p, unsigned char* ws) {
     const Tables& tb = p->tb[0];
@@ -1126,11 +1119,12 @@ pp_status run_plain(pp_plan p, const Tio* f, Tio* u, unsigned char* ws, hipStrea
     double* partial = reinterpret_cast<double*>(ws + p->o_partial);
     cplx<T>* S = reinterpret_cast<cplx<T>*>(ws + p->o_S);
     const double npts = (double)p->nx * p->ny * p->nz;
+    int records = 0;   // partial records per batch entry of the last x kernel
     pp_status st;
     if ((st = mark(p, s, 0)) != PP_OK) return st;
-    PP_HIP((pp::launch_xfwd<T, Tio, T>(f, S, partial, xa, p->batch, faces, s)));
+    PP_HIP((pp::launch_xfwd<T, Tio, T>(f, S, partial, xa, p->batch, faces, &records, s)));
     if ((st = mark(p, s, 3)) != PP_OK) return st;
-    PP_HIP(pp::launch_finalize_xfwd(partial, x_records(p, false), p->batch, npts,
+    PP_HIP(pp::launch_finalize_xfwd(partial, records, p->batch, npts,
                                     sc + pp::SC_COUNT + 3 * p->batch, sc + pp::SC_MAXF, s));
     if ((st = mark(p, s, 1)) != PP_OK) return st;
     PP_HIP(pp::launch_mid<T>(S, ma, p->batch, s));
@@ -1209,23 +1203,24 @@ pp_status run_refined(pp_plan p, const double* f, double* u, unsigned char* ws, 
     }
     const bool keep_u0 = p->ir_max > 0;   // with no correction the float solve goes straight to u
 
+    int records = 0;   // partial records per batch entry of the last x kernel
     pp_status st;
     if ((st = mark(p, s, 3)) != PP_OK) return st;
     PP_HIP(pp::launch_ir_init(sc, p->batch, s));
     if ((st = mark(p, s, 0)) != PP_OK) return st;
-    PP_HIP((pp::launch_xfwd<double, double, float>(f, S, partial, xa64, p->batch, faces, s)));
+    PP_HIP((pp::launch_xfwd<double, double, float>(f, S, partial, xa64, p->batch, faces, &records, s)));
     if ((st = mark(p, s, 3)) != PP_OK) return st;
-    PP_HIP(pp::launch_finalize_xfwd(partial, x_records(p, false), p->batch, npts, sc + pp::SC_COUNT + 3 * p->batch,
+    PP_HIP(pp::launch_finalize_xfwd(partial, records, p->batch, npts, sc + pp::SC_COUNT + 3 * p->batch,
                                     sc + pp::SC_MAXF, s));
     if ((st = mark(p, s, 1)) != PP_OK) return st;
     if ((st = refined_mid(p, ws, ma, ma64, s)) != PP_OK) return st;
     ma.mu = sc + pp::SC_COUNT;   // corrections project their own right-hand side
     ma64.mu = sc + pp::SC_COUNT;
     if ((st = mark(p, s, 2)) != PP_OK) return st;
-    if (keep_u0) PP_HIP(pp::launch_xinv_first(S, u0, xa, p->batch, sc, region, partial, s));
-    else PP_HIP(pp::launch_xinv_update(S, u, nullptr, xa, p->batch, sc, region, partial, pp::XINV_FIRST, s));
+    if (keep_u0) PP_HIP(pp::launch_xinv_first(S, u0, xa, p->batch, sc, region, partial, &records, s));
+    else PP_HIP(pp::launch_xinv_update(S, u, nullptr, xa, p->batch, sc, region, partial, pp::XINV_FIRST, &records, s));
     if ((st = mark(p, s, 3)) != PP_OK) return st;
-    PP_HIP(pp::launch_finalize_update(partial, x_records(p, true), p->batch, nregion, sc, 1, s));
+    PP_HIP(pp::launch_finalize_update(partial, records, p->batch, nregion, sc, 1, s));
     if ((st = mark(p, s, -1)) != PP_OK) return st;
     p->last_iters = 0;
     p->last_rel = 1.0;
@@ -1240,28 +1235,28 @@ pp_status run_refined(pp_plan p, const double* f, double* u, unsigned char* ws, 
             xr.ihy2 = ra.ihy2;
             xr.ihz2 = ra.ihz2;
             if ((st = mark(p, s, 0)) != PP_OK) return st;
-            PP_HIP(pp::launch_xfwd_res(f, S, partial, xr, p->batch, faces, s));
+            PP_HIP(pp::launch_xfwd_res(f, S, partial, xr, p->batch, faces, &records, s));
         } else if (fused) {
             if ((st = mark(p, s, 3)) != PP_OK) return st;
             PP_HIP((pp::launch_residual<double, float>(f, u, r32, ra, sc, s)));
             if ((st = mark(p, s, 0)) != PP_OK) return st;
-            PP_HIP((pp::launch_xfwd<double, float, float>(r32, S, partial, xa64, p->batch, nullptr, s)));
+            PP_HIP((pp::launch_xfwd<double, float, float>(r32, S, partial, xa64, p->batch, nullptr, &records, s)));
         } else {
             if ((st = mark(p, s, 3)) != PP_OK) return st;
             if (it == 1) PP_HIP((pp::launch_residual<float, double>(f, u0, r64, ra, sc, s)));
             else PP_HIP((pp::launch_residual<double, double>(f, u, r64, ra, sc, s)));
             if ((st = mark(p, s, 0)) != PP_OK) return st;
-            PP_HIP((pp::launch_xfwd<double, double, float>(r64, S, partial, xa64, p->batch, nullptr, s)));
+            PP_HIP((pp::launch_xfwd<double, double, float>(r64, S, partial, xa64, p->batch, nullptr, &records, s)));
         }
         if ((st = mark(p, s, 3)) != PP_OK) return st;
-        PP_HIP(pp::launch_finalize_xfwd(partial, x_records(p, false), p->batch, npts, sc + pp::SC_COUNT, nullptr, s));
+        PP_HIP(pp::launch_finalize_xfwd(partial, records, p->batch, npts, sc + pp::SC_COUNT, nullptr, s));
         if ((st = mark(p, s, 1)) != PP_OK) return st;
         if ((st = refined_mid(p, ws, ma, ma64, s)) != PP_OK) return st;
         if ((st = mark(p, s, 2)) != PP_OK) return st;
         PP_HIP(pp::launch_xinv_update(S, u, it == 1 ? u0 : nullptr, xa, p->batch, sc, region, partial,
-                                      pp::XINV_UPDATE, s));
+                                      pp::XINV_UPDATE, &records, s));
         if ((st = mark(p, s, 3)) != PP_OK) return st;
-        PP_HIP(pp::launch_finalize_update(partial, x_records(p, true), p->batch, nregion, sc, 0, s));
+        PP_HIP(pp::launch_finalize_update(partial, records, p->batch, nregion, sc, 0, s));
         if ((st = mark(p, s, -1)) != PP_OK) return st;
         double h[8];
         PP_HIP(hipMemcpyAsync(h, sc, sizeof(h), hipMemcpyDeviceToHost, s));

@@ -24,7 +24,6 @@ constexpr int kEpt = 8;
 constexpr int kXGroups = 4;
 constexpr int xdir_waves(int nx) { return nx <= 512 ? 1 : (nx <= 1024 ? 2 : 4); }
 constexpr int xdir_threads(int nx) { return 64 * kXGroups * xdir_waves(nx); }
-constexpr int kXBlocksPerCU = 2;               // persistent x-kernel workgroups per CU
 constexpr int kXLdsBytes = 96 * 1024;          // x-kernel LDS target (lines + twiddle tables), two workgroups per CU
 constexpr int kXLdsMax = 160 * 1024 - 1024;    // x-kernel LDS ceiling (one workgroup per CU)
 constexpr int kXVals = kEpt;                   // values per lane of one line (64 xdir_waves(nx) kXVals >= nx)
@@ -203,27 +202,23 @@ struct ResidualArgs {
 };
 
 // --- launchers (return hipError_t of the launch) -----------------------------
-// Row blocks of the x kernels and the persistent grid they run on; the x kernels
-// write one partial record per (batch entry, workgroup, wavefront).
+// Row blocks of the x kernels.  They run on a persistent grid (never larger than
+// the row blocks) and write one partial record per (batch entry, workgroup,
+// wavefront): the launchers return the records per batch entry.
 int x_blocks(int ny, int ty, int nz, int batch);
-int x_grid(int nblocks);
-// Grid of an x-kernel launch over nblocks row blocks: when the workgroups take
-// blocks in pairs (the inverse kernel with float spectra, x_next_block), half
-// as many are needed.
-int x_launch_grid(int nblocks, bool paired);
 
 // faces: null, or the face values to lift into the source as it is read.
 // T: arithmetic; Tin: source; Ts: spectra (T, or float with the double slots of XArgs::slo).
 template <typename T, typename Tin, typename Ts>
 hipError_t launch_xfwd(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
-                       const FaceArgs<Tin>* faces, hipStream_t s);
+                       const FaceArgs<Tin>* faces, int* records, hipStream_t s);
 // The forward transform of the refinement residual r = f - lift - c - L_h u0
 // (XArgs::u0, sc, fbc, proj, ih*2), computed as the rows are read: double
 // arithmetic, float spectra with the double slots.  Rows of at most 512
 // (res_fused_supported); other shapes take launch_residual + launch_xfwd.
 bool res_fused_supported(int nx);
 hipError_t launch_xfwd_res(const double* f, cplx<float>* S, double* partial, const XArgs<double>& a, int batch,
-                           const FaceArgs<double>* faces, hipStream_t s);
+                           const FaceArgs<double>* faces, int* records, hipStream_t s);
 
 template <typename T, typename Tout>
 hipError_t launch_xinv(const cplx<T>* S, Tout* u, const XArgs<T>& a, int batch, const double* shift,
@@ -237,9 +232,10 @@ hipError_t launch_xinv(const cplx<T>* S, Tout* u, const XArgs<T>& a, int batch, 
 //                       XINV_UPDATE: u = prev + d / scale - cmean - gauge_shift[b],
 //                       prev = uprev (float) when given, else u itself.
 hipError_t launch_xinv_first(const cplx<float>* S, float* u0, const XArgs<float>& a, int batch, const double* scalars,
-                             int gauge_region, double* partial, hipStream_t s);
+                             int gauge_region, double* partial, int* records, hipStream_t s);
 hipError_t launch_xinv_update(const cplx<float>* S, double* u, const float* uprev, const XArgs<float>& a, int batch,
-                              const double* scalars, int gauge_region, double* partial, int mode, hipStream_t s);
+                              const double* scalars, int gauge_region, double* partial, int mode, int* records,
+                              hipStream_t s);
 
 template <typename T>
 hipError_t launch_mid(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s);

@@ -23,10 +23,12 @@
 // Writing columns with y contiguous is the x <-> y transpose, done through LDS
 // so that both the row reads and the column writes are coalesced.
 
+#include <map>
 #include <mutex>
 #include <set>
 #include <tuple>
 #include <type_traits>
+#include <utility>
 
 #include "pp_kernels.hpp"
 
@@ -824,12 +826,6 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
     return r;
 }
 
-// Allow the kernel the dynamic LDS it may ask for (lines + twiddle tables)
-// (the template argument is the kernel itself).
-template <auto K> static hipError_t allow_lds() {
-    return allow_dynamic_lds(reinterpret_cast<const void*>(K), kXLdsMax);
-}
-
 int device_cus() {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
@@ -839,15 +835,57 @@ int device_cus() {
     return cus;
 }
 
-// Persistent grid: a few resident workgroups per CU.
-int x_grid(int nblocks) {
-    const int cus = device_cus();
-    return nblocks < cus * kXBlocksPerCU ? nblocks : cus * kXBlocksPerCU;
+// Workgroups of kernel K (`threads`, `lds` bytes of dynamic LDS, which it is
+// allowed here) that one CU holds; asked of the runtime once per (kernel,
+// device, LDS size).
+template <auto K> static hipError_t x_resident(int threads, size_t lds, int* out) {
+    static std::mutex mu;
+    static std::map<std::pair<int, size_t>, int> known;   // (device, LDS bytes)
+    const void* k = reinterpret_cast<const void*>(K);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto it = known.find({dev, lds});
+    if (it != known.end()) {
+        *out = it->second;
+        return hipSuccess;
+    }
+    e = allow_dynamic_lds(k, kXLdsMax);
+    if (e != hipSuccess) return e;
+    int n = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, lds);
+    if (e != hipSuccess) return e;
+    *out = known[{dev, lds}] = n < 1 ? 1 : n;
+    return hipSuccess;
 }
+
+// Persistent grid over nblocks row blocks (pairs of them for the inverse
+// kernels with float spectra, x_next_block).  As many workgroups per CU as are
+// resident, up to four; where that is one or two, twice as many, since the
+// second set starts as the first ones end, out of step with one another.
+// Measured against two per CU throughout (x forward / inverse): 553 x 256 x 216
+// f64 200 / 213 -> 154 / 171 us, 200 x 288 x 486 f32 147 / 144 -> 107 / 94,
+// 256^3 f64 80 / 80 -> 66 / 64, 512^3 f32 273 / 282 -> 227 / 271.  The
+// exact-count kernels with double data (and the refined solve's) keep two where
+// the source and the spectra are past the 256 MiB last-level cache: they are bound by HBM, and more
+// workgroups only spread their rows (384^3 x 4 inverse 793 -> 866 us with
+// three; 512^3 unchanged).
+static int x_grid(int nblocks, bool paired, int resident, bool two) {
+    const int per = two ? 2 : (resident >= 3 ? (resident < 4 ? resident : 4) : 2 * resident);
+    const int work = paired ? (nblocks + 1) / 2 : nblocks;
+    const int most = device_cus() * per;
+    return work < most ? work : most;
+}
+// Source and spectra of a launch past the last-level cache.
+template <typename A, typename B, typename T> static bool x_far(const XArgs<T>& a, int batch) {
+    const size_t points = (size_t)a.nx * a.ny * a.nz * batch;
+    return points * (sizeof(A) + sizeof(B)) > ((size_t)256 << 20);
+}
+
 
 int x_blocks(int ny, int ty, int nz, int batch) { return ((ny + ty - 1) / ty) * nz * batch; }
 
-int x_launch_grid(int nblocks, bool paired) { return x_grid(paired ? (nblocks + 1) / 2 : nblocks); }
 
 // Row blocks of the FULL shape: nx = 64 WPL RMAX, one line per group of
 // wavefronts, whole blocks in y.  (None for four wavefronts per line: at 1024
@@ -858,23 +896,29 @@ template <int WPL, int RMAX, typename T> static bool x_full(const XArgs<T>& a) {
 
 template <typename T, typename Tin, typename Ts, int WPL, int RMAX, bool FACES, bool RES = false>
 static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
-                                    const FaceArgs<Tin>& fa, hipStream_t s) {
+                                    const FaceArgs<Tin>& fa, int* records, hipStream_t s) {
     const int nb = x_blocks(a.ny, a.ty, a.nz, batch);
+    constexpr int threads = 64 * kXGroups * WPL;
+    int resident = 1;
     if constexpr (WPL <= 2) {
         if (x_full<WPL, RMAX>(a)) {
-            const hipError_t le = allow_lds<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>();
+            const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
+            const int grid = x_grid(nb, false, resident, sizeof(T) == 8 && x_far<Tin, Ts>(a, batch));
+            *records = grid * kXGroups * WPL;
             hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>),
-                               dim3(x_launch_grid(nb, false)), dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, f, S, partial, a,
+                               dim3(grid), dim3(threads), x_lds_bytes(a), s, f, S, partial, a,
                                nb, fa);
             return hipGetLastError();
         }
     }
     {
-        const hipError_t le = allow_lds<k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>>();
-        if (le != hipSuccess) return le;
-        hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>), dim3(x_launch_grid(nb, false)),
-                           dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, f, S, partial, a, nb, fa);
+        const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>>(threads, x_lds_bytes(a), &resident);
+            if (le != hipSuccess) return le;
+            const int grid = x_grid(nb, false, resident, false);
+            *records = grid * kXGroups * WPL;
+        hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>), dim3(grid),
+                           dim3(threads), x_lds_bytes(a), s, f, S, partial, a, nb, fa);
     }
     return hipGetLastError();
 }
@@ -882,60 +926,66 @@ static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, 
 bool res_fused_supported(int nx) { return nx <= 512; }
 
 hipError_t launch_xfwd_res(const double* f, cplx<float>* S, double* partial, const XArgs<double>& a, int batch,
-                           const FaceArgs<double>* faces, hipStream_t s) {
+                           const FaceArgs<double>* faces, int* records, hipStream_t s) {
     if (a.nx > 512) return hipErrorInvalidValue;
     const FaceArgs<double> none{};
     if (faces) {
-        if (a.nx == 256) return launch_xfwd_shape<double, double, float, 1, 4, true, true>(f, S, partial, a, batch, *faces, s);
-        if (a.nx == 384) return launch_xfwd_shape<double, double, float, 1, 6, true, true>(f, S, partial, a, batch, *faces, s);
-        return launch_xfwd_shape<double, double, float, 1, 8, true, true>(f, S, partial, a, batch, *faces, s);
+        if (a.nx == 256) return launch_xfwd_shape<double, double, float, 1, 4, true, true>(f, S, partial, a, batch, *faces, records, s);
+        if (a.nx == 384) return launch_xfwd_shape<double, double, float, 1, 6, true, true>(f, S, partial, a, batch, *faces, records, s);
+        return launch_xfwd_shape<double, double, float, 1, 8, true, true>(f, S, partial, a, batch, *faces, records, s);
     }
-    if (a.nx == 256) return launch_xfwd_shape<double, double, float, 1, 4, false, true>(f, S, partial, a, batch, none, s);
-    if (a.nx == 384) return launch_xfwd_shape<double, double, float, 1, 6, false, true>(f, S, partial, a, batch, none, s);
-    return launch_xfwd_shape<double, double, float, 1, 8, false, true>(f, S, partial, a, batch, none, s);
+    if (a.nx == 256) return launch_xfwd_shape<double, double, float, 1, 4, false, true>(f, S, partial, a, batch, none, records, s);
+    if (a.nx == 384) return launch_xfwd_shape<double, double, float, 1, 6, false, true>(f, S, partial, a, batch, none, records, s);
+    return launch_xfwd_shape<double, double, float, 1, 8, false, true>(f, S, partial, a, batch, none, records, s);
 }
 
 template <typename T, typename Tin, typename Ts, bool FACES>
 static hipError_t launch_xfwd_any(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
-                                  const FaceArgs<Tin>& fa, hipStream_t s) {
+                                  const FaceArgs<Tin>& fa, int* records, hipStream_t s) {
     // exact-count forms: rows of 256 = 64 x 4, 384 = 64 x 6, 512 = 64 x 8, 768 =
     // 128 x 6, 1024 = 128 x 8
-    if (a.nx == 256) return launch_xfwd_shape<T, Tin, Ts, 1, 4, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx == 384) return launch_xfwd_shape<T, Tin, Ts, 1, 6, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx <= 512) return launch_xfwd_shape<T, Tin, Ts, 1, 8, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx == 768) return launch_xfwd_shape<T, Tin, Ts, 2, 6, FACES>(f, S, partial, a, batch, fa, s);
-    if (a.nx <= 1024) return launch_xfwd_shape<T, Tin, Ts, 2, 8, FACES>(f, S, partial, a, batch, fa, s);
-    return launch_xfwd_shape<T, Tin, Ts, 4, 8, FACES>(f, S, partial, a, batch, fa, s);
+    if (a.nx == 256) return launch_xfwd_shape<T, Tin, Ts, 1, 4, FACES>(f, S, partial, a, batch, fa, records, s);
+    if (a.nx == 384) return launch_xfwd_shape<T, Tin, Ts, 1, 6, FACES>(f, S, partial, a, batch, fa, records, s);
+    if (a.nx <= 512) return launch_xfwd_shape<T, Tin, Ts, 1, 8, FACES>(f, S, partial, a, batch, fa, records, s);
+    if (a.nx == 768) return launch_xfwd_shape<T, Tin, Ts, 2, 6, FACES>(f, S, partial, a, batch, fa, records, s);
+    if (a.nx <= 1024) return launch_xfwd_shape<T, Tin, Ts, 2, 8, FACES>(f, S, partial, a, batch, fa, records, s);
+    return launch_xfwd_shape<T, Tin, Ts, 4, 8, FACES>(f, S, partial, a, batch, fa, records, s);
 }
 
 template <typename T, typename Tin, typename Ts>
 hipError_t launch_xfwd(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
-                       const FaceArgs<Tin>* faces, hipStream_t s) {
-    if (faces) return launch_xfwd_any<T, Tin, Ts, true>(f, S, partial, a, batch, *faces, s);
+                       const FaceArgs<Tin>* faces, int* records, hipStream_t s) {
+    if (faces) return launch_xfwd_any<T, Tin, Ts, true>(f, S, partial, a, batch, *faces, records, s);
     const FaceArgs<Tin> none{};
-    return launch_xfwd_any<T, Tin, Ts, false>(f, S, partial, a, batch, none, s);
+    return launch_xfwd_any<T, Tin, Ts, false>(f, S, partial, a, batch, none, records, s);
 }
 
 template <typename T, typename Tout, typename Tp, int MODE, int WPL, int RMAX>
 static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, const XArgs<T>& a, int batch,
                                     const double* shift, const double* scalars, int gauge_region, double* partial,
-                                    hipStream_t s) {
+                                    int* records, hipStream_t s) {
     const int nb = x_blocks(a.ny, a.ty, a.nz, batch);
+    constexpr int threads = 64 * kXGroups * WPL;
+    int resident = 1;
     if constexpr (WPL <= 2) {
         if (x_full<WPL, RMAX>(a)) {
-            const hipError_t le = allow_lds<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>();
+            const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
+            const int grid = x_grid(nb, sizeof(T) == 4, resident, (sizeof(Tout) == 8 || MODE != XINV_STORE) && x_far<T, Tout>(a, batch));
+            if (records) *records = grid * kXGroups * WPL;
             hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>),
-                               dim3(x_launch_grid(nb, sizeof(T) == 4)), dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, S, u,
+                               dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u,
                                uprev, a, shift, scalars, gauge_region, partial, nb);
             return hipGetLastError();
         }
     }
     {
-        const hipError_t le = allow_lds<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>>();
-        if (le != hipSuccess) return le;
+        const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>>(threads, x_lds_bytes(a), &resident);
+            if (le != hipSuccess) return le;
+            const int grid = x_grid(nb, sizeof(T) == 4, resident, false);
+            if (records) *records = grid * kXGroups * WPL;
         hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>),
-                           dim3(x_launch_grid(nb, sizeof(T) == 4)), dim3(64 * kXGroups * WPL), x_lds_bytes(a), s, S, u, uprev,
+                           dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u, uprev,
                            a, shift, scalars, gauge_region, partial, nb);
     }
     return hipGetLastError();
@@ -944,11 +994,11 @@ static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, 
 template <typename T, typename Tout, typename Tp, int MODE>
 static hipError_t launch_xinv_any(const cplx<T>* S, Tout* u, const Tp* uprev, const XArgs<T>& a, int batch,
                                   const double* shift, const double* scalars, int gauge_region, double* partial,
-                                  hipStream_t s) {
+                                  int* records, hipStream_t s) {
     // exact-count forms as in launch_xfwd_any
     auto go = [&](auto wpl, auto rmax) {
         return launch_xinv_shape<T, Tout, Tp, MODE, decltype(wpl)::value, decltype(rmax)::value>(
-            S, u, uprev, a, batch, shift, scalars, gauge_region, partial, s);
+            S, u, uprev, a, batch, shift, scalars, gauge_region, partial, records, s);
     };
     using std::integral_constant;
     if (a.nx == 256) return go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
@@ -962,39 +1012,39 @@ static hipError_t launch_xinv_any(const cplx<T>* S, Tout* u, const Tp* uprev, co
 template <typename T, typename Tout>
 hipError_t launch_xinv(const cplx<T>* S, Tout* u, const XArgs<T>& a, int batch, const double* shift, hipStream_t s) {
     return launch_xinv_any<T, Tout, Tout, XINV_STORE>(S, u, (const Tout*)nullptr, a, batch, shift,
-                                                      (const double*)nullptr, 0, (double*)nullptr, s);
+                                                      (const double*)nullptr, 0, (double*)nullptr, nullptr, s);
 }
 
 hipError_t launch_xinv_first(const cplx<float>* S, float* u0, const XArgs<float>& a, int batch, const double* scalars,
-                             int gauge_region, double* partial, hipStream_t s) {
+                             int gauge_region, double* partial, int* records, hipStream_t s) {
     // no mean shift: u0 holds the transform's own float values, so storing it
     // rounds nothing; the gauge shift of the first update removes the mean
     return launch_xinv_any<float, float, float, XINV_FIRST>(S, u0, (const float*)nullptr, a, batch,
-                                                            (const double*)nullptr, scalars, gauge_region, partial, s);
+                                                            (const double*)nullptr, scalars, gauge_region, partial, records, s);
 }
 
 hipError_t launch_xinv_update(const cplx<float>* S, double* u, const float* uprev, const XArgs<float>& a, int batch,
-                              const double* scalars, int gauge_region, double* partial, int mode, hipStream_t s) {
+                              const double* scalars, int gauge_region, double* partial, int mode, int* records, hipStream_t s) {
     const double* shift = scalars + SC_COUNT + batch;   // cmean of the correction solve
     if (mode == XINV_FIRST)
         return launch_xinv_any<float, double, double, XINV_FIRST>(S, u, (const double*)nullptr, a, batch, shift,
-                                                                  scalars, gauge_region, partial, s);
+                                                                  scalars, gauge_region, partial, records, s);
     if (uprev)
         return launch_xinv_any<float, double, float, XINV_UPDATE>(S, u, uprev, a, batch, shift, scalars,
-                                                                  gauge_region, partial, s);
+                                                                  gauge_region, partial, records, s);
     return launch_xinv_any<float, double, double, XINV_UPDATE>(S, u, (const double*)nullptr, a, batch, shift, scalars,
-                                                               gauge_region, partial, s);
+                                                               gauge_region, partial, records, s);
 }
 
 template hipError_t launch_xfwd<double, double, double>(const double*, cplx<double>*, double*, const XArgs<double>&,
-                                                        int, const FaceArgs<double>*, hipStream_t);
+                                                        int, const FaceArgs<double>*, int*, hipStream_t);
 template hipError_t launch_xfwd<float, float, float>(const float*, cplx<float>*, double*, const XArgs<float>&, int,
-                                                     const FaceArgs<float>*, hipStream_t);
+                                                     const FaceArgs<float>*, int*, hipStream_t);
 // refined solve: double arithmetic, float spectra (and the double slots)
 template hipError_t launch_xfwd<double, double, float>(const double*, cplx<float>*, double*, const XArgs<double>&,
-                                                       int, const FaceArgs<double>*, hipStream_t);
+                                                       int, const FaceArgs<double>*, int*, hipStream_t);
 template hipError_t launch_xfwd<double, float, float>(const float*, cplx<float>*, double*, const XArgs<double>&, int,
-                                                      const FaceArgs<float>*, hipStream_t);
+                                                      const FaceArgs<float>*, int*, hipStream_t);
 template hipError_t launch_xinv<double, double>(const cplx<double>*, double*, const XArgs<double>&, int,
                                                 const double*, hipStream_t);
 template hipError_t launch_xinv<float, float>(const cplx<float>*, float*, const XArgs<float>&, int, const double*,
