@@ -85,6 +85,7 @@ struct pp_plan_s {
     // make it large, and the automatic choice then keeps one march per column
     double split_gmax = 0.0;
     bool plane_ok = false;   // a plane fits the one-workgroup transforms (plane.hip)
+    bool lines_ok = false;   // else: y lines fit the separate y transforms
     // refined solve: slots lo0 .. lo0+nlo-1 kept in double by the x transform and the z march
     int lo0 = 0, nlo = 0;
     // the first correction's size may stand for the refinement's contraction
@@ -517,10 +518,8 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
     };
     twiddles(p->fx, &tb.t_twx, &tb.t_mkx);
     twiddles(p->fy, &tb.t_twy, &tb.t_mky);
-    if (p->plane_ok) {
-        fft_twiddles(p->fxp, &tb.t_twxp);
-        fft_twiddles(p->fyp, &tb.t_twyp);
-    }
+    if (p->plane_ok) fft_twiddles(p->fxp, &tb.t_twxp);
+    if (p->plane_ok || p->lines_ok) fft_twiddles(p->fyp, &tb.t_twyp);
 
     std::vector<double> lamx(nx), lamy(ny);
     for (int k = 0; k < nx; ++k) lamx[k] = eigenvalue(p->bx, k, nx, p->h[0]);
@@ -1084,6 +1083,43 @@ bool use_planes(pp_plan p) {
            (p->dtype == PP_F64 || p->split_gmax <= kSplitGMax);
 }
 
+// The z stage in three passes (y transforms by themselves around the z-systems
+// in one pass) instead of the march, where the march would run one workgroup
+// per column (periodic z; double columns too close to singular to split; more
+// columns than the splits are for) with few of them.  Its time is then that of
+// one column, nz long, whatever their number, while the passes take time by the
+// (column, entry) pairs of a plane.  Measured, march and passes: periodic z, f64
+// 200 x 384 x 256 337 and 279 us (49,152 pairs), 256 x 256 x 384 362 and 370
+// (49,152), 256^3 338 and 246 (32,768); f32 256 x 256 x 384 285 and 201
+// (49,152), 200 x 384 x 384 310 and 290 (73,728), 512 x 256 x 512 607 and 692
+// (65,536); on lines of 512, whose march keeps stages in registers, f64
+// 200 x 512 x 128 253 and 216 (32,768), 200 x 512 x 192 254 and 297.
+template <typename T> bool use_lines(pp_plan p, const pp::MidArgs<T>& ma) {
+    const long long pairs = (long long)p->slots * p->batch * p->ny;
+    const long long most = p->ny == 512 ? 32768 : (sizeof(T) == 8 ? 45056 : 61440);
+    return p->lines_ok && p->zsolver == 0 && p->zsplit_mode == PP_ZSPLIT_AUTO && ma.zsplit == 0 && ma.zsegs == 0 &&
+           pairs <= most;
+}
+
+template <typename T>
+pp_status run_lines(pp_plan p, cplx<T>* S, const pp::MidArgs<T>& ma, unsigned char* ws, hipStream_t s) {
+    const Tables& tb = p->tb[0];
+    const unsigned char* t = ws + p->o_tab[0];
+    pp::LineArgs<T> la{};
+    la.ny = p->ny;
+    la.slots = p->slots;
+    la.bx = p->bx;
+    la.by = p->by;
+    la.nlines = (size_t)p->batch * p->nz * p->slots;
+    la.fy = p->fyp;
+    la.twy = reinterpret_cast<const cplx<T>*>(t + tb.t_twyp);
+    la.mky = reinterpret_cast<const cplx<T>*>(t + tb.t_mky);
+    PP_HIP(pp::launch_ylines<T>(S, la, false, s));
+    PP_HIP(pp::launch_zscan<T>(S, ma, pp::ScanArgs{}, p->batch, s));
+    PP_HIP(pp::launch_ylines<T>(S, la, true, s));
+    return PP_OK;
+}
+
 template <typename T>
 pp_status run_planes(pp_plan p, const T* f, T* u, unsigned char* ws, hipStream_t s, bool project, bool demean,
                      const pp::FaceArgs<T>* faces) {
@@ -1114,6 +1150,7 @@ pp_status run_plain(pp_plan p, const Tio* f, Tio* u, unsigned char* ws, hipStrea
     if (use_planes(p)) return run_planes<T>(p, f, u, ws, s, project, demean, faces);
     pp::XArgs<T> xa = make_xargs<T>(p, ws);
     pp::MidArgs<T> ma = make_midargs<T>(p, ws, project, demean);
+    const bool lines = use_lines(p, ma);
     xa.zends = ma.zsplit > 0;
     double* sc = reinterpret_cast<double*>(ws + p->o_scalars);
     double* partial = reinterpret_cast<double*>(ws + p->o_partial);
@@ -1127,7 +1164,11 @@ pp_status run_plain(pp_plan p, const Tio* f, Tio* u, unsigned char* ws, hipStrea
     PP_HIP(pp::launch_finalize_xfwd(partial, records, p->batch, npts,
                                     sc + pp::SC_COUNT + 3 * p->batch, sc + pp::SC_MAXF, s));
     if ((st = mark(p, s, 1)) != PP_OK) return st;
-    PP_HIP(pp::launch_mid<T>(S, ma, p->batch, s));
+    if (lines) {
+        if ((st = run_lines<T>(p, S, ma, ws, s)) != PP_OK) return st;
+    } else {
+        PP_HIP(pp::launch_mid<T>(S, ma, p->batch, s));
+    }
     if ((st = mark(p, s, 2)) != PP_OK) return st;
     PP_HIP((pp::launch_xinv<T, Tio>(S, u, xa, p->batch, sc + pp::SC_COUNT + p->batch, s)));
     return mark(p, s, -1);
@@ -1495,6 +1536,9 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
     if (p->plane_ok) {
         p->fxp = plane_radices(nx, plane_threads > pp::kPlaneSmallThreads);
         p->fyp = plane_radices(ny, plane_threads > pp::kPlaneSmallThreads);
+    } else if (dtype != PP_F32_REFINED && ny <= pp::kLineMax) {
+        p->lines_ok = true;
+        p->fyp = plane_radices(ny, true);
     }
     if (f64) build_tables<double>(p, p->tb[0]);
     else build_tables<float>(p, p->tb[0]);

@@ -150,7 +150,7 @@ __device__ __forceinline__ void plane_stage(cplx<T>* buf, int ld, int nl, float 
 
 // Transform nl lines of d.n values, ld apart (nl d.n <= EPT NTH).  Radices up
 // to 16 (plane_radices()): a stage costs a pass through LDS and two barriers.
-template <int EPT, int NTH, bool INV, typename T>
+template <int EPT, int NTH, bool INV, typename T, bool BIG = (NTH > kPlaneSmallThreads)>
 __device__ __forceinline__ void plane_fft(cplx<T>* buf, int ld, int nl, const FftDesc& d, const cplx<T>* tw) {
     const float inv_nl = 1.0f / (float)nl;
     int Ls = 1, tid = threadIdx.x;
@@ -161,10 +161,10 @@ __device__ __forceinline__ void plane_fft(cplx<T>* buf, int ld, int nl, const Ff
         asm volatile("" : "+v"(tid));
         // (small planes, 256 threads, are launch-bound: more code than radix 8
         // costs them more than the stages it saves, 32^3 forward 7.6 -> 8.8 us)
-        if (NTH > kPlaneSmallThreads && R == 16) plane_stage<16, cdiv(EPT, 16), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
-        else if (NTH > kPlaneSmallThreads && R == 12) plane_stage<12, cdiv(EPT, 12), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
-        else if (NTH > kPlaneSmallThreads && R == 9) plane_stage<9, cdiv(EPT, 9), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
-        else if (NTH > kPlaneSmallThreads && R == 6) plane_stage<6, cdiv(EPT, 6), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
+        if (BIG && R == 16) plane_stage<16, cdiv(EPT, 16), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
+        else if (BIG && R == 12) plane_stage<12, cdiv(EPT, 12), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
+        else if (BIG && R == 9) plane_stage<9, cdiv(EPT, 9), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
+        else if (BIG && R == 6) plane_stage<6, cdiv(EPT, 6), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
         else if (R == 8) plane_stage<8, cdiv(EPT, 8), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
         else if (R == 4) plane_stage<4, cdiv(EPT, 4), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
         else if (R == 3) plane_stage<3, cdiv(EPT, 3), NTH, INV, T>(buf, ld, nl, inv_nl, d.n, Ls, tw, tid);
@@ -211,6 +211,19 @@ __device__ __forceinline__ cplx<T> plane_dct_bin(const cplx<T>* line, const cplx
     const cplx<T> vr = line[k == 0 ? 0 : N - k];
     const cplx<T> w = mk_[k];
     return cscale(cadd(cmul(w, vk), cmulc(vr, w)), T(0.5));
+}
+
+// Entry e of a transformed y line: its DCT bin, or its DFT bin; with `pair`, two
+// real x spectra share the line: A_k -> entry k, B_k -> entry N-k (k < N/2).
+template <typename T>
+__device__ __forceinline__ cplx<T> plane_bin(const cplx<T>* line, int e, int N, bool dct, bool pair,
+                                             const cplx<T>* mk_) {
+    if (dct) return plane_dct_bin<T>(line, mk_, e, N);
+    const cplx<T> v = line[e];
+    if (!pair || e == 0 || 2 * e == N) return v;
+    const cplx<T> w = line[N - e];
+    return 2 * e < N ? mk<T>(T(0.5) * (v.x + w.x), T(0.5) * (v.y - w.y))
+                     : mk<T>(T(0.5) * (w.y + v.y), T(0.5) * (v.x - w.x));
 }
 
 template <int NW> __device__ __forceinline__ void plane_partial(double acc, double* red, double* out) {
@@ -344,19 +357,26 @@ __global__ __launch_bounds__(NTH) void k_plane_fwd(const T* __restrict__ f, cplx
     for (int i = tid; i < a.slots * ny; i += NTH) {
         const int m = qdiv(i, inv_ny), e = i - mul24(m, ny);
         const cplx<T>* line = L.buf + mul24(m, a.ldy);
-        cplx<T> v;
-        if (a.by != BC_P) {
-            v = plane_dct_bin<T>(line, L.mky, e, ny);
-        } else {
-            v = line[e];
-            if ((a.bx != BC_P || m == 0) && e != 0 && 2 * e != ny) {
-                // two real x spectra in one line: A_k -> entry k, B_k -> entry ny-k (k < ny/2)
-                const cplx<T> w = line[ny - e];
-                v = 2 * e < ny ? mk<T>(T(0.5) * (v.x + w.x), T(0.5) * (v.y - w.y))
-                               : mk<T>(T(0.5) * (w.y + v.y), T(0.5) * (v.x - w.x));
-            }
-        }
-        dst[i] = v;
+        dst[i] = plane_bin<T>(line, e, ny, a.by != BC_P, a.by == BC_P && (a.bx != BC_P || m == 0), L.mky);
+    }
+}
+
+// Pre-processing of one pair (k, N-k), k > 0, of a line for the inverse transform.
+template <typename T>
+__device__ __forceinline__ void plane_pre_pair(cplx<T>* line, int k, int N, bool dct, const cplx<T>* mk_) {
+    if (2 * k > N) return;
+    const cplx<T> a = line[k];
+    if (2 * k == N) {
+        if (dct) line[k] = cmulc(mk<T>(a.x + a.y, a.y - a.x), mk_[k]);
+        return;
+    }
+    const cplx<T> b = line[N - k];
+    if (dct) {
+        line[k] = cmulc(mk<T>(a.x + b.y, a.y - b.x), mk_[k]);
+        line[N - k] = cmulc(mk<T>(b.x + a.y, b.y - a.x), mk_[N - k]);
+    } else {
+        line[k] = mk<T>(a.x - b.y, a.y + b.x);
+        line[N - k] = mk<T>(a.x + b.y, b.x - a.y);
     }
 }
 
@@ -370,20 +390,7 @@ __device__ __forceinline__ void plane_pre(cplx<T>* buf, int ld, int nl, int N, b
     for (int q = threadIdx.x; q < nl * hn; q += NTH) {
         const int l = qdiv(q, inv_hn), k = q - mul24(l, hn);
         cplx<T>* line = buf + mul24(l, ld);
-        if (k == 0 || 2 * k > N) continue;
-        const cplx<T> a = line[k];
-        if (2 * k == N) {
-            if (dct) line[k] = cmulc(mk<T>(a.x + a.y, a.y - a.x), mk_[k]);
-            continue;
-        }
-        const cplx<T> b = line[N - k];
-        if (dct) {
-            line[k] = cmulc(mk<T>(a.x + b.y, a.y - b.x), mk_[k]);
-            line[N - k] = cmulc(mk<T>(b.x + a.y, b.y - a.x), mk_[N - k]);
-        } else {
-            line[k] = mk<T>(a.x - b.y, a.y + b.x);
-            line[N - k] = mk<T>(a.x + b.y, b.x - a.y);
-        }
+        if (k != 0) plane_pre_pair<T>(line, k, N, dct, mk_);
     }
     lds_barrier();
 }
@@ -494,6 +501,85 @@ __global__ __launch_bounds__(NTH) void k_plane_inv(const cplx<T>* __restrict__ S
 }
 
 // ---------------------------------------------------------------------------
+// The y transforms of spectral lines by themselves, in place (grids whose planes
+// do not fit in LDS and whose columns are too few for the z march): a workgroup
+// takes a group of whole lines (b, z, slot), kLineVals values per thread.
+// ---------------------------------------------------------------------------
+template <typename T> constexpr int kLineVals = sizeof(T) == 8 ? 8 : 16;
+
+template <typename T, int NTH, bool INV>
+__global__ __launch_bounds__(NTH) void k_ylines(cplx<T>* __restrict__ S, LineArgs<T> a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int V = kLineVals<T>;
+    const int ny = a.ny, ld = a.ld, tid = threadIdx.x;
+    const size_t first = (size_t)blockIdx.x * a.group;
+    const int nl = (int)(a.nlines - first < (size_t)a.group ? a.nlines - first : (size_t)a.group);
+    cplx<T>* buf = reinterpret_cast<cplx<T>*>(smem);
+    cplx<T>* tw = buf + a.group * ld;
+    cplx<T>* mk_ = tw + ny;
+    cplx<T>* col = S + first * ny;
+    const float inv_ny = 1.0f / (float)ny;
+    const int n = nl * ny;
+    cplx<T> v[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const int i = tid + k * NTH;
+        v[k] = i < n ? col[i] : mk<T>(T(0), T(0));
+    }
+    for (int i = tid; i < ny; i += NTH) {
+        tw[i] = a.twy[i];
+        if (a.by != BC_P) mk_[i] = a.mky[i];
+    }
+    // the slot of a line decides whether its two parts are separate real spectra
+    const float inv_slots = 1.0f / (float)a.slots;
+    const int slot0 = (int)(first % (size_t)a.slots);
+    auto paired = [&](int l) {
+        if (a.bx != BC_P) return true;
+        const int q = slot0 + l;
+        return q - mul24(qdiv(q, inv_slots), a.slots) == 0;
+    };
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const int i = tid + k * NTH;
+        if (i < n) {
+            const int l = qdiv(i, inv_ny), y = i - mul24(l, ny);
+            int pos = y;
+            cplx<T> x = v[k];
+            if (!INV && a.by != BC_P) {
+                pos = makhoul_pos(y, ny);
+                if (a.by == BC_D && (y & 1)) x = mk<T>(-x.x, -x.y);
+            }
+            buf[mul24(l, ld) + pos] = x;
+        }
+    }
+    lds_barrier();
+    if constexpr (INV) {
+        // pairs (k, ny-k) of every line; periodic y: only of lines that hold two real spectra
+        const int hn = (ny >> 1) + 1;
+        const float inv_hn = 1.0f / (float)hn;
+        for (int q = tid; q < nl * hn; q += NTH) {
+            const int l = qdiv(q, inv_hn), k = q - mul24(l, hn);
+            if (k == 0 || (a.by == BC_P && !paired(l))) continue;
+            plane_pre_pair<T>(buf + mul24(l, ld), k, ny, a.by != BC_P, mk_);
+        }
+        lds_barrier();
+    }
+    plane_fft<V, NTH, INV, T, true>(buf, ld, nl, a.fy, tw);
+    for (int i = tid; i < n; i += NTH) {
+        const int l = qdiv(i, inv_ny), y = i - mul24(l, ny);
+        const cplx<T>* line = buf + mul24(l, ld);
+        cplx<T> x;
+        if constexpr (INV) {
+            x = line[a.by != BC_P ? makhoul_pos(y, ny) : y];
+            if (a.by == BC_D && (y & 1)) x = mk<T>(-x.x, -x.y);
+        } else {
+            x = plane_bin<T>(line, y, ny, a.by != BC_P, a.by == BC_P && paired(l), mk_);
+        }
+        col[i] = x;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // z-systems in one pass.  Both sweeps of the Thomas algorithm are first-order
 // recurrences with tabulated factors,
 //     y_z = (d_z - y_{z-1}) w_z,      u_z = y_z - w_z u_{z+1},
@@ -529,7 +615,9 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     // the planes' sums of the source (k_plane_fwd), by the first column's
     // workgroup; a source with an Inf or NaN gives a mean that is not finite
     T proj = T(0);
-    if (tile == 0) {
+    if (!g.partial) {
+        if (sing && a.project) proj = (T)(a.hz2 * a.mu[b]);
+    } else if (tile == 0) {
         double s = 0.0;
         for (int i = tid; i < nz; i += nth) s += g.partial[(size_t)b * nz + i];
 #pragma unroll
@@ -805,6 +893,25 @@ hipError_t launch_plane_inv(const cplx<T>* S, T* u, const PlaneArgs<T>& a, int b
     return run_plane_inv<T, 1024>(S, u, a, batch, shift, s);
 }
 
+template <typename T, int NTH>
+static hipError_t run_ylines(cplx<T>* S, LineArgs<T> a, bool inverse, hipStream_t s) {
+    a.ld = a.ny | 1;
+    a.group = kLineVals<T> * NTH / a.ny;
+    if ((size_t)a.group > a.nlines) a.group = (int)a.nlines;
+    const size_t lds = ((size_t)a.group * a.ld + (size_t)(a.by != BC_P ? 2 : 1) * a.ny) * sizeof(cplx<T>);
+    const dim3 grid((unsigned)((a.nlines + a.group - 1) / a.group));
+    const hipError_t e = inverse ? plane_allow<k_ylines<T, NTH, true>>() : plane_allow<k_ylines<T, NTH, false>>();
+    if (e != hipSuccess) return e;
+    if (inverse) hipLaunchKernelGGL((k_ylines<T, NTH, true>), grid, dim3(NTH), lds, s, S, a);
+    else hipLaunchKernelGGL((k_ylines<T, NTH, false>), grid, dim3(NTH), lds, s, S, a);
+    return hipGetLastError();
+}
+
+// Groups of 2048 (double) or 4096 (float) values: four lines of 512 and up.
+template <typename T> hipError_t launch_ylines(cplx<T>* S, const LineArgs<T>& a, bool inverse, hipStream_t s) {
+    return run_ylines<T, 256>(S, a, inverse, s);
+}
+
 template <typename T, int L, bool PERZ, bool ONE>
 static hipError_t run_zscan(cplx<T>* S, const MidArgs<T>& a, const ScanArgs& g, int batch, hipStream_t s) {
     const int ct = 1 << g.lct;
@@ -843,6 +950,7 @@ template <typename T> hipError_t launch_zscan(cplx<T>* S, const MidArgs<T>& a, S
                                             const FaceArgs<T>*, hipStream_t);                                      \
     template hipError_t launch_plane_inv<T>(const cplx<T>*, T*, const PlaneArgs<T>&, int, const double*,           \
                                             hipStream_t);                                                          \
+    template hipError_t launch_ylines<T>(cplx<T>*, const LineArgs<T>&, bool, hipStream_t);                         \
     template hipError_t launch_zscan<T>(cplx<T>*, const MidArgs<T>&, ScanArgs, int, hipStream_t);
 PP_PLANE_INST(double)
 PP_PLANE_INST(float)

@@ -180,8 +180,18 @@ template <typename T> struct PlaneArgs {
 // Fill in the shape of the plane kernels; false if the plane does not fit.
 template <typename T> bool plane_shape(PlaneArgs<T>& a);
 
+// y transforms of whole spectral lines by themselves (plane.hip).
+constexpr int kLineMax = 512;        // longest line
+template <typename T> struct LineArgs {
+    int ny, slots, bx, by;
+    int ld, group;           // LDS stride, lines per workgroup (chosen by the launcher)
+    size_t nlines;           // lines of the spectral array (batch nz slots)
+    FftDesc fy;
+    const cplx<T>*twy, *mky;
+};
+
 struct ScanArgs {
-    const double* partial;   // sum of the source per (batch entry, plane)
+    const double* partial;   // sum of the source per (batch entry, plane); null: the means are in MidArgs::mu
     double npts;             // points per batch entry
     double* mu;              // [batch] source means (output)
     double* maxf;            // a value that is finite where the source is (output)
@@ -248,6 +258,7 @@ hipError_t launch_plane_fwd(const T* f, cplx<T>* S, double* partial, const Plane
 template <typename T>
 hipError_t launch_plane_inv(const cplx<T>* S, T* u, const PlaneArgs<T>& a, int batch, const double* shift,
                             hipStream_t s);
+template <typename T> hipError_t launch_ylines(cplx<T>* S, const LineArgs<T>& a, bool inverse, hipStream_t s);
 template <typename T> hipError_t launch_zscan(cplx<T>* S, const MidArgs<T>& a, ScanArgs g, int batch, hipStream_t s);
 
 // Compute units of the current device (256 if the query fails).

@@ -111,3 +111,45 @@ def test_plane_z_in_chunks(bc):
         banner(f"plane chunks {dtype} {bc} {shape}")
         u, _ = _solve(f, bc, h, dtype)
         assert rel_max(u, oracle.solve(f, bc, h, "mean")) < TOL[dtype], (dtype, shape)
+
+
+# (nz, ny, nx) off the small-plane rule (a line over 256) whose march would be one
+# workgroup per column with few columns: y transforms by themselves.  Groups of
+# lines whole and ragged, odd lines, one line of 512 per quarter group, z in one
+# pass and in chunks
+LINES = [(5, 8, 288), (3, 9, 324), (4, 288, 8), (3, 512, 4), (6, 243, 288), (17, 4, 512), (1025, 2, 288)]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("bc", ["PPPPPP", "NNDDPP", "DDNNPP", "NNPPPP", "PPNNPP"])
+def test_separate_y_transforms_vs_oracle_and_march(dtype, bc):
+    from gpu_util import banner, rel_max
+    rng = np.random.default_rng(1 + sum(map(ord, bc + dtype)))
+    for shape in LINES:
+        banner(f"lines {dtype} {bc} {shape}")
+        h = (1.0 / shape[2], 1.0 / shape[1], 1.0 / shape[0])
+        if shape[0] > 1000:
+            h = (1.0 / 64, 1.0 / 64, 1.0 / 64)
+        f = _input(rng, shape, dtype)
+        u, _ = _solve(f, bc, h, dtype)
+        u1, _ = _solve(f, bc, h, dtype, zsplit="off")
+        uo = oracle.solve(f, bc, h, "mean")
+        assert rel_max(u, uo) < TOL[dtype], (dtype, bc, shape)
+        assert rel_max(u1, uo) < TOL[dtype], (dtype, bc, shape)
+
+
+@pytest.mark.parametrize("gauge", ["mean", "pin", "pin_raw"])
+def test_separate_y_transforms_near_singular_batch(gauge):
+    """Double columns too close to singular to split (long z, Neumann), per batch entry."""
+    from gpu_util import banner, rel_max
+    rng = np.random.default_rng(53)
+    shape, bc = (700, 4, 288), "NNPPNN"
+    h = (1.0 / 64, 1.0 / 64, 1.0 / 64)
+    f = rng.standard_normal((2,) + shape) + np.array([0.5, -1.0])[:, None, None, None]
+    banner(f"lines near-singular {gauge} {shape}")
+    u, plan = _solve(f, bc, h, "f64", gauge=gauge, batch=2)
+    _, means, _ = plan.last_info()
+    for b in range(2):
+        assert rel_max(u[b], oracle.solve(f[b], bc, h, gauge)) < 1e-12, (b, gauge)
+        expect = f[b].mean() if gauge != "pin_raw" else 0.0
+        assert abs(means[b] - expect) < 1e-13 * max(1.0, abs(f[b]).max())
