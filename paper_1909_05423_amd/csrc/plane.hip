@@ -611,6 +611,38 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     cplx<T>* col = S + (size_t)b * a.slots * nz * ny + (size_t)m * a.sstride + e;
     const size_t zs = (size_t)a.zstride;
     const bool sing = a.singular && c == 0;
+    const cplx<T> zero = mk<T>(T(0), T(0));
+
+    // rows of this thread's segment in the chunk at z0 (past the end: the last
+    // row), issued before anything else is waited for
+    cplx<T> y[L], w[L];
+    auto rows = [&](int z0) __attribute__((always_inline)) {
+        const int zb = z0 + seg * L;
+#pragma unroll
+        for (int r = 0; r < L; ++r) y[r] = col[(size_t)(zb + r < nz ? zb + r : nz - 1) * zs];
+    };
+    rows(0);
+    cplx<T> winf = zero, wlast = zero;
+    int elen = 0, roff = 0;
+    if (on) {
+        winf = a.winf[(size_t)m * ny + e];
+        wlast = a.wlast[(size_t)m * ny + e];
+        elen = a.elen[(size_t)m * ny + e];
+        roff = a.rowoff[m];
+    }
+    int alen = 0, qlen = 0, aoff = 0, qoff = 0;   // periodic z: this column's rows of alpha and qp
+    cplx<T> qlast = zero, ig = zero, id = zero;
+    if constexpr (PERZ) {
+        if (on) {
+            alen = a.aelen[(size_t)m * ny + e];
+            qlen = a.qelen[(size_t)m * ny + e];
+            aoff = a.aoff[m];
+            qoff = a.qoff[m];
+            qlast = a.qlast[(size_t)m * ny + e];
+            ig = a.inv_gamma[(size_t)m * ny + e];
+            id = a.inv_den[(size_t)m * ny + e];
+        }
+    }
 
     // the planes' sums of the source (k_plane_fwd), by the first column's
     // workgroup; a source with an Inf or NaN gives a mean that is not finite
@@ -635,32 +667,41 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
         lds_barrier();
     }
 
-    const cplx<T> zero = mk<T>(T(0), T(0));
-    cplx<T> winf = zero, wlast = zero;
-    int elen = 0, roff = 0;
-    if (on) {
-        winf = a.winf[(size_t)m * ny + e];
-        wlast = a.wlast[(size_t)m * ny + e];
-        elen = a.elen[(size_t)m * ny + e];
-        roff = a.rowoff[m];
-    }
-    cplx<T> y[L], w[L];
-    auto load = [&](int z0) __attribute__((always_inline)) {
+    // Eight rows from zb of a table that holds `len` of them from row `off`; past
+    // them the value `past`.  One branch for the eight (skipped by a wavefront
+    // whose columns have none left): a branch per row waits for each load by
+    // itself (200 x 192 x 256 f32 periodic: 45 -> 31 us).
+    constexpr int H = 8;
+    static_assert(L % H == 0, "rows in groups of eight");
+    auto table = [&](const cplx<T>* rows_, int off, int len, int zb, cplx<T> past, cplx<T>* t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < H; ++r) t[r] = past;
+        if (__builtin_amdgcn_ballot_w64(zb < len)) {
+            cplx<T> q[H];
+#pragma unroll
+            for (int r = 0; r < H; ++r) q[r] = rows_[zb + r < len ? (size_t)(off + zb + r) * ny + e : 0];
+#pragma unroll
+            for (int r = 0; r < H; ++r) {
+                const bool tab = zb + r < len;
+                t[r] = mk<T>(tab ? q[r].x : past.x, tab ? q[r].y : past.y);
+            }
+        }
+    };
+    // pivots of the thread's rows in the chunk at z0, and rows past the end made inert
+    auto pivots = [&](int z0) __attribute__((always_inline)) {
+        const int zb = z0 + seg * L;
+#pragma unroll
+        for (int h = 0; h < L; h += H) table(a.wrows, roff, elen, zb + h, winf, w + h);
 #pragma unroll
         for (int r = 0; r < L; ++r) {
-            const int z = z0 + seg * L + r;
-            y[r] = zero;
-            w[r] = zero;
-            if (on && z < nz) y[r] = col[(size_t)z * zs];
+            const int z = zb + r;
+            const bool last = z == nz - 1, in = on && z < nz;
+            w[r] = mk<T>(in ? (last ? wlast.x : w[r].x) : T(0), in ? (last ? wlast.y : w[r].y) : T(0));
         }
 #pragma unroll
         for (int r = 0; r < L; ++r) {
-            const int z = z0 + seg * L + r;
-            if (on && z < nz) {
-                cplx<T> p = winf;
-                if (z < elen) p = a.wrows[(size_t)(roff + z) * ny + e];
-                w[r] = mk<T>(z == nz - 1 ? wlast.x : p.x, z == nz - 1 ? wlast.y : p.y);
-            }
+            const bool in = on && zb + r < nz;
+            y[r] = mk<T>(in ? y[r].x : T(0), in ? y[r].y : T(0));
         }
     };
     // Chain the segments' maps from `carry`, the value entering the chunk (at
@@ -711,21 +752,29 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     const int nch = ONE ? 1 : g.chunks;
     for (int ch = 0; ch < nch; ++ch) {
         const int z0 = ch * P * L;
-        load(z0);
+        if (ch > 0) rows(z0);
+        pivots(z0);
+#pragma unroll
+        for (int r = 0; r < L; ++r) {
+            y[r] = cscale(y[r], a.scale);
+            if (sing && z0 + seg * L + r < nz) y[r].x -= proj;
+        }
+        if constexpr (PERZ) {
+#pragma unroll
+            for (int h = 0; h < L; h += H) {
+                cplx<T> al[H];
+                table(a.arows, aoff, alen, z0 + seg * L + h, zero, al);
+#pragma unroll
+                for (int r = 0; r < H; ++r) {
+                    y0.x += al[r].x * y[h + r].x;
+                    y0.y += al[r].y * y[h + r].y;
+                }
+            }
+        }
         cplx<T> A = mk<T>(T(1), T(1)), prev = zero;
 #pragma unroll
         for (int r = 0; r < L; ++r) {
-            const int z = z0 + seg * L + r;
-            cplx<T> d = cscale(y[r], a.scale);
-            if (sing && z < nz) d.x -= proj;
-            if constexpr (PERZ) {
-                if (on && z < nz && z < a.aelen[(size_t)m * ny + e]) {
-                    const cplx<T> al = a.arows[(size_t)(a.aoff[m] + z) * ny + e];
-                    y0.x += al.x * d.x;
-                    y0.y += al.y * d.y;
-                }
-            }
-            prev = mk<T>((d.x - prev.x) * w[r].x, (d.y - prev.y) * w[r].y);
+            prev = mk<T>((y[r].x - prev.x) * w[r].x, (y[r].y - prev.y) * w[r].y);
             y[r] = prev;
             A = mk<T>(-w[r].x * A.x, -w[r].y * A.y);
         }
@@ -762,7 +811,6 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
         for (int q = 0; q < nw; ++q) s = cadd(s, sB[q * ct + cl]);
         if (on) {
             const cplx<T> yl = sA[cl];
-            const cplx<T> ig = a.inv_gamma[(size_t)m * ny + e], id = a.inv_den[(size_t)m * ny + e];
             corr = mk<T>((s.x + yl.x * ig.x) * id.x, (s.y + yl.y * ig.y) * id.y);
         }
         lds_barrier();
@@ -770,19 +818,19 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     carry = zero;
     for (int ch = nch - 1; ch >= 0; --ch) {
         const int z0 = ch * P * L;
-        if constexpr (!ONE) load(z0);
+        if constexpr (!ONE) {
+            rows(z0);
+            pivots(z0);
+        }
         if constexpr (PERZ) {
-            if (on) {
-                const int ql = a.qelen[(size_t)m * ny + e];
-                const cplx<T> qlast = a.qlast[(size_t)m * ny + e];
 #pragma unroll
-                for (int r = 0; r < L; ++r) {
-                    const int z = z0 + seg * L + r;
-                    if (z < ql && z < nz - 1) {
-                        const cplx<T> q = a.qrows[(size_t)(a.qoff[m] + z) * ny + e];
-                        y[r] = mk<T>(y[r].x - corr.x * q.x, y[r].y - corr.y * q.y);
-                    }
-                    if (z == nz - 1) y[r] = mk<T>(y[r].x - corr.x * qlast.x, y[r].y - corr.y * qlast.y);
+            for (int h = 0; h < L; h += H) {
+                cplx<T> q[H];
+                table(a.qrows, qoff, qlen, z0 + seg * L + h, zero, q);
+#pragma unroll
+                for (int r = 0; r < H; ++r) {
+                    if (z0 + seg * L + h + r == nz - 1) q[r] = qlast;
+                    y[h + r] = mk<T>(y[h + r].x - corr.x * q[r].x, y[h + r].y - corr.y * q[r].y);
                 }
             }
         }
@@ -922,23 +970,26 @@ static hipError_t run_zscan(cplx<T>* S, const MidArgs<T>& a, const ScanArgs& g, 
     return hipGetLastError();
 }
 
-// Columns per workgroup: 128 bytes of every plane (whole lines) where z is
-// long enough to fill a workgroup with its segments, twice that below.  Rows
-// per thread: 8 up to 128 planes (more threads per column, shorter chains),
-// else 16; longer columns than a workgroup holds go in chunks.
+// Columns per workgroup: 128 bytes of every plane (whole lines), twice that
+// where the segments of so few would not fill a wavefront; small workgroups,
+// since a CU holds 12 to 16 wavefronts of these kernels (200 x 192 x 256 f32
+// periodic, 13 segments: 60 us with 32 columns, one workgroup of 7 wavefronts per
+// CU).  Rows per thread: 8 up to 128 planes (more threads per column, shorter
+// recurrences) and in double with periodic z (16 spill), else 16; longer columns than a workgroup holds go in chunks.
 template <typename T> hipError_t launch_zscan(cplx<T>* S, const MidArgs<T>& a, ScanArgs g, int batch, hipStream_t s) {
     const int base = sizeof(T) == 8 ? 3 : 4;
-    const int L = a.nz <= 128 ? 8 : 16;
+    const int L = (a.nz <= 128 || (a.zper && sizeof(T) == 8)) ? 8 : 16;
     int P = (a.nz + L - 1) / L;
-    g.lct = P >= 16 ? base : base + 1;
+    g.lct = (P << base) >= 64 ? base : base + 1;
     const int pmax = kScanThreads >> g.lct;
     g.chunks = (P + pmax - 1) / pmax;
     if (g.chunks > 1) P = pmax;
     g.segs = P;
     if (a.zper) {
-        if (L == 8) return run_zscan<T, 8, true, true>(S, a, g, batch, s);
-        if (g.chunks == 1) return run_zscan<T, 16, true, true>(S, a, g, batch, s);
-        return run_zscan<T, 16, true, false>(S, a, g, batch, s);
+        if (L == 8 && g.chunks == 1) return run_zscan<T, 8, true, true>(S, a, g, batch, s);
+        constexpr int LP = sizeof(T) == 8 ? 8 : 16;
+        if (g.chunks == 1) return run_zscan<T, LP, true, true>(S, a, g, batch, s);
+        return run_zscan<T, LP, true, false>(S, a, g, batch, s);
     }
     if (L == 8) return run_zscan<T, 8, false, true>(S, a, g, batch, s);
     if (g.chunks == 1) return run_zscan<T, 16, false, true>(S, a, g, batch, s);
