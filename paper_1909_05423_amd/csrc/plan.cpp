@@ -171,30 +171,6 @@ bool factor23(int n) {
     return n == 1;
 }
 
-// Radix plan: as many radix-8 stages as possible (two radix-4 stages instead
-// of an 8 and a 2), then radix 3.
-pp::FftDesc radix_plan(int n) {
-    pp::FftDesc d{};
-    d.n = n;
-    int a = 0, b = 0, m = n;
-    while (m % 2 == 0) { m /= 2; ++a; }
-    while (m % 3 == 0) { m /= 3; ++b; }
-    int s = 0;
-    int n8 = a / 3, rem = a % 3;
-    if (rem == 1 && n8 >= 1) {
-        for (int i = 0; i < n8 - 1; ++i) d.radix[s++] = 8;
-        d.radix[s++] = 4;
-        d.radix[s++] = 4;
-    } else {
-        for (int i = 0; i < n8; ++i) d.radix[s++] = 8;
-        if (rem == 1) d.radix[s++] = 2;
-        if (rem == 2) d.radix[s++] = 4;
-    }
-    for (int i = 0; i < b; ++i) d.radix[s++] = 3;
-    d.nstages = s;
-    return d;
-}
-
 // Radices of a line of the plane kernels (plane.hip): as few stages as 2, 3, 4
 // and 8, and for big planes also 6, 9, 12 and 16, allow (each is a pass through
 // LDS), and of those plans the one of the smallest largest radix.
@@ -1461,8 +1437,8 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
     p->slots = (nx + 1) / 2;
     const bool f64 = (dtype == PP_F64);
     p->elem = f64 ? sizeof(cplx<double>) : sizeof(cplx<float>);
-    p->fx = radix_plan(nx);
-    p->fy = radix_plan(ny);
+    p->fx = pp::fft_plan(nx, pp::x_nine(dtype != PP_F32, pp::xdir_waves(nx)), false);   // (refined: double forward)
+    p->fy = pp::fft_plan(ny, false, false);
     p->ldl = pp::padded_len(nx);
     p->ldy = pp::padded_len(ny);
     // row pairs (lines) per x workgroup: each group of wavefronts transforms lpw
@@ -1495,6 +1471,7 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
         return PP_ERR_SIZE;
     }
     p->ty = 2 * lines;
+    if (pp::x_exact(nx, ny, p->ty)) p->fx = pp::fft_plan(nx, true, true);
     // partial records per batch entry: one per (workgroup, wavefront) of the persistent
     // x kernels, whose grid never exceeds the row blocks of all batch entries
     p->nper = (size_t)((ny + p->ty - 1) / p->ty) * nz * batch * pp::kXGroups * pp::xdir_waves(nx);

@@ -28,79 +28,6 @@ __device__ __forceinline__ int mul24(int a, int b) { return (int)__umul24((unsig
 // fdiv with the half folded into the multiply-add: floor(i / n), inv = 1.0f / n.
 __device__ __forceinline__ int qdiv(int i, float inv) { return (int)fmaf((float)i, inv, 0.5f * inv); }
 
-// exp(-2 pi i M / N) (conjugated for the inverse) times a, M and N known at
-// compile time (N 9, 12 or 16: the inner twiddles of the composite butterflies).
-constexpr double kCos[3][16] = {
-    {1.0, 0.76604444311897803520, 0.17364817766693034885, -0.5, -0.93969262078590838405},
-    {1.0, 0.86602540378443864676, 0.5, 0.0, -0.5, -0.86602540378443864676, -1.0},
-    {1.0, 0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173, 0.0, -0.38268343236508977173,
-     -0.70710678118654752440, -0.92387953251128675613, -1.0, -0.92387953251128675613}};
-constexpr double kSin[3][16] = {
-    {0.0, 0.64278760968653932632, 0.98480775301220805937, 0.86602540378443864676, 0.34202014332566873304},
-    {0.0, 0.5, 0.86602540378443864676, 1.0, 0.86602540378443864676, 0.5, 0.0},
-    {0.0, 0.38268343236508977173, 0.70710678118654752440, 0.92387953251128675613, 1.0, 0.92387953251128675613,
-     0.70710678118654752440, 0.38268343236508977173, 0.0, -0.38268343236508977173}};
-template <int M, int N, bool INV, typename T> __device__ __forceinline__ cplx<T> twist(cplx<T> a) {
-    if constexpr (M == 0) return a;
-    else if constexpr (4 * M == N) return rot<INV>(a);
-    else if constexpr (2 * M == N) return mk<T>(-a.x, -a.y);
-    else {
-        constexpr int t = N == 9 ? 0 : (N == 12 ? 1 : 2);
-        constexpr T c = (T)kCos[t][M], s = (T)(INV ? kSin[t][M] : -kSin[t][M]);
-        return mk<T>(a.x * c - a.y * s, a.x * s + a.y * c);
-    }
-}
-
-// DFT of A B values from DFTs of A and B values:
-// X[k + A l] = sum_n w_{AB}^{n k} w_B^{n l} sum_m x[m B + n] w_A^{m k}.
-template <int A, int B, bool INV, typename T, int n> __device__ __forceinline__ void composite_column(cplx<T>* v) {
-    if constexpr (n < B) {
-        cplx<T> u[A];
-#pragma unroll
-        for (int m = 0; m < A; ++m) u[m] = v[m * B + n];
-        bfly<A, INV, T>(u);
-        v[n] = u[0];
-        v[B + n] = twist<n, A * B, INV, T>(u[1]);
-        if constexpr (A > 2) v[2 * B + n] = twist<2 * n, A * B, INV, T>(u[2]);
-        if constexpr (A > 3) v[3 * B + n] = twist<3 * n, A * B, INV, T>(u[3]);
-        composite_column<A, B, INV, T, n + 1>(v);
-    }
-}
-template <int A, int B, bool INV, typename T> __device__ __forceinline__ void bfly_composite(cplx<T>* v) {
-    composite_column<A, B, INV, T, 0>(v);
-    cplx<T> w[A * B];
-#pragma unroll
-    for (int k = 0; k < A; ++k) {
-        bfly<B, INV, T>(v + k * B);
-#pragma unroll
-        for (int l = 0; l < B; ++l) w[k + A * l] = v[k * B + l];
-    }
-#pragma unroll
-    for (int i = 0; i < A * B; ++i) v[i] = w[i];
-}
-template <int R, bool INV, typename T> __device__ __forceinline__ void plane_bfly(cplx<T>* v) {
-    if constexpr (R == 6) {
-        // 2 x 3 by the coprime split: no inner twiddles (inputs (3 m + 2 n) mod 6, outputs (3 k + 4 l) mod 6)
-        cplx<T> a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
-        bfly3<INV, T>(a);
-        bfly3<INV, T>(b);
-        v[0] = cadd(a[0], b[0]);
-        v[3] = csub(a[0], b[0]);
-        v[4] = cadd(a[1], b[1]);
-        v[1] = csub(a[1], b[1]);
-        v[2] = cadd(a[2], b[2]);
-        v[5] = csub(a[2], b[2]);
-    } else if constexpr (R == 9) {
-        bfly_composite<3, 3, INV, T>(v);
-    } else if constexpr (R == 12) {
-        bfly_composite<3, 4, INV, T>(v);
-    } else if constexpr (R == 16) {
-        bfly_composite<4, 4, INV, T>(v);
-    } else {
-        bfly<R, INV, T>(v);
-    }
-}
-
 // One Stockham stage (see wfft_stage) of all `nl` lines of a plane by the whole
 // workgroup.  Consecutive lanes take the same butterfly of consecutive lines,
 // whose stride is odd: no bank conflicts at any stage without padding inside
@@ -133,7 +60,7 @@ __device__ __forceinline__ void plane_stage(cplx<T>* buf, int ld, int nl, float 
                     v[i][t] = INV ? cmulc(v[i][t], w) : cmul(v[i][t], w);
                 }
             }
-            plane_bfly<R, INV, T>(v[i]);
+            rbfly<R, INV, T>(v[i]);
             dst[i] = row + (j - k) * R + k;
         }
     }

@@ -153,12 +153,118 @@ template <int R, bool INV, typename T> __device__ __forceinline__ void bfly(cplx
     else bfly8<INV, T>(v);
 }
 
-// Radix plan of one transform length, fixed on the host.
+// exp(-2 pi i M / N) (conjugated for the inverse) times a, M and N known at
+// compile time (N 9, 12 or 16: the inner twiddles of the composite butterflies).
+constexpr double kCos[3][16] = {
+    {1.0, 0.76604444311897803520, 0.17364817766693034885, -0.5, -0.93969262078590838405},
+    {1.0, 0.86602540378443864676, 0.5, 0.0, -0.5, -0.86602540378443864676, -1.0},
+    {1.0, 0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173, 0.0, -0.38268343236508977173,
+     -0.70710678118654752440, -0.92387953251128675613, -1.0, -0.92387953251128675613}};
+constexpr double kSin[3][16] = {
+    {0.0, 0.64278760968653932632, 0.98480775301220805937, 0.86602540378443864676, 0.34202014332566873304},
+    {0.0, 0.5, 0.86602540378443864676, 1.0, 0.86602540378443864676, 0.5, 0.0},
+    {0.0, 0.38268343236508977173, 0.70710678118654752440, 0.92387953251128675613, 1.0, 0.92387953251128675613,
+     0.70710678118654752440, 0.38268343236508977173, 0.0, -0.38268343236508977173}};
+template <int M, int N, bool INV, typename T> __device__ __forceinline__ cplx<T> twist(cplx<T> a) {
+    if constexpr (M == 0) return a;
+    else if constexpr (4 * M == N) return rot<INV>(a);
+    else if constexpr (2 * M == N) return mk<T>(-a.x, -a.y);
+    else {
+        constexpr int t = N == 9 ? 0 : (N == 12 ? 1 : 2);
+        constexpr T c = (T)kCos[t][M], s = (T)(INV ? kSin[t][M] : -kSin[t][M]);
+        return mk<T>(a.x * c - a.y * s, a.x * s + a.y * c);
+    }
+}
+
+// DFT of A B values from DFTs of A and B values:
+// X[k + A l] = sum_n w_{AB}^{n k} w_B^{n l} sum_m x[m B + n] w_A^{m k}.
+template <int A, int B, bool INV, typename T, int n> __device__ __forceinline__ void composite_column(cplx<T>* v) {
+    if constexpr (n < B) {
+        cplx<T> u[A];
+#pragma unroll
+        for (int m = 0; m < A; ++m) u[m] = v[m * B + n];
+        bfly<A, INV, T>(u);
+        v[n] = u[0];
+        v[B + n] = twist<n, A * B, INV, T>(u[1]);
+        if constexpr (A > 2) v[2 * B + n] = twist<2 * n, A * B, INV, T>(u[2]);
+        if constexpr (A > 3) v[3 * B + n] = twist<3 * n, A * B, INV, T>(u[3]);
+        composite_column<A, B, INV, T, n + 1>(v);
+    }
+}
+template <int A, int B, bool INV, typename T> __device__ __forceinline__ void bfly_composite(cplx<T>* v) {
+    composite_column<A, B, INV, T, 0>(v);
+    cplx<T> w[A * B];
+#pragma unroll
+    for (int k = 0; k < A; ++k) {
+        bfly<B, INV, T>(v + k * B);
+#pragma unroll
+        for (int l = 0; l < B; ++l) w[k + A * l] = v[k * B + l];
+    }
+#pragma unroll
+    for (int i = 0; i < A * B; ++i) v[i] = w[i];
+}
+template <int R, bool INV, typename T> __device__ __forceinline__ void rbfly(cplx<T>* v) {
+    if constexpr (R == 6) {
+        // 2 x 3 by the coprime split: no inner twiddles (inputs (3 m + 2 n) mod 6, outputs (3 k + 4 l) mod 6)
+        cplx<T> a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
+        bfly3<INV, T>(a);
+        bfly3<INV, T>(b);
+        v[0] = cadd(a[0], b[0]);
+        v[3] = csub(a[0], b[0]);
+        v[4] = cadd(a[1], b[1]);
+        v[1] = csub(a[1], b[1]);
+        v[2] = cadd(a[2], b[2]);
+        v[5] = csub(a[2], b[2]);
+    } else if constexpr (R == 9) {
+        bfly_composite<3, 3, INV, T>(v);
+    } else if constexpr (R == 12) {
+        bfly_composite<3, 4, INV, T>(v);
+    } else if constexpr (R == 16) {
+        bfly_composite<4, 4, INV, T>(v);
+    } else {
+        bfly<R, INV, T>(v);
+    }
+}
+
+// Radices of one transform length.
 struct FftDesc {
     int n;
     int nstages;
     int radix[16];
 };
+
+// The radices of an x or y line: as few stages as possible from 8, 4, 3 and 2,
+// and for some x rows also 9 (`nine`, see x_nine; 288 = 9 8 4 instead of 8 4 3 3,
+// 486 = 9 9 3 2 instead of 3 3 3 3 3 2) and, where the exact-count kernels run, 6 (`six`; 384 =
+// 8 8 6 instead of 8 4 4 3); of those plans the one of the smallest sum, larger
+// radices first.  (6 in the kernels of any length costs them registers, 125 ->
+// 139, and a workgroup per CU.)
+constexpr void fft_search(int m, int largest, bool nine, bool six, FftDesc& d, int sum, FftDesc& best, int& best_sum) {
+    if (m == 1) {
+        if (d.nstages < best.nstages || (d.nstages == best.nstages && sum < best_sum)) {
+            best = d;
+            best_sum = sum;
+        }
+        return;
+    }
+    if (d.nstages >= 15 || d.nstages >= best.nstages) return;
+    const int radix[6] = {9, 8, 6, 4, 3, 2};
+    for (int i = 0; i < 6; ++i) {
+        const int r = radix[i];
+        if (r > largest || m % r || (r == 9 && !nine) || (r == 6 && !six)) continue;
+        d.radix[d.nstages++] = r;
+        fft_search(m / r, r, nine, six, d, sum + r, best, best_sum);
+        d.radix[--d.nstages] = 0;
+    }
+}
+constexpr FftDesc fft_plan(int n, bool nine, bool six) {
+    FftDesc best{}, d{};
+    best.nstages = 16;
+    int best_sum = 0;
+    fft_search(n, 9, nine, six, d, 0, best, best_sum);
+    best.n = n;
+    return best;
+}
 
 constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 
@@ -244,7 +350,7 @@ __device__ __forceinline__ void wfft_stage(cplx<T>* line, int N, int Ls, const c
                     v[i][t] = INV ? cmulc(v[i][t], w) : cmul(v[i][t], w);
                 }
             }
-            bfly<R, INV, T>(v[i]);
+            rbfly<R, INV, T>(v[i]);
             dst[i] = (j - k) * R + k;
         }
     }
@@ -263,7 +369,7 @@ __device__ __forceinline__ void wfft_stage(cplx<T>* line, int N, int Ls, const c
 // RECOMP: the LDS addresses of a stage are formed anew in every stage.  Without
 // it the compiler keeps those of all four radices in registers across the
 // stages, which is right only for kernels with registers to spare.
-template <int EPL, bool INV, typename T, bool RECOMP = false, int LW = 64>
+template <int EPL, bool INV, typename T, bool RECOMP = false, int LW = 64, bool NINE = false>
 __device__ __forceinline__ void wfft(cplx<T>* line, const FftDesc& d, const cplx<T>* tw, int lane,
                                      bool active = true) {
     int Ls = 1;
@@ -273,9 +379,62 @@ __device__ __forceinline__ void wfft(cplx<T>* line, const FftDesc& d, const cplx
         if (R == 8) wfft_stage<8, cdiv(EPL, 8), INV, LW, T>(line, d.n, Ls, tw, lane, active);
         else if (R == 4) wfft_stage<4, cdiv(EPL, 4), INV, LW, T>(line, d.n, Ls, tw, lane, active);
         else if (R == 3) wfft_stage<3, cdiv(EPL, 3), INV, LW, T>(line, d.n, Ls, tw, lane, active);
+        else if (NINE && R == 9) wfft_stage<9, cdiv(EPL, 9), INV, LW, T>(line, d.n, Ls, tw, lane, active);
         else wfft_stage<2, cdiv(EPL, 2), INV, LW, T>(line, d.n, Ls, tw, lane, active);
         Ls *= R;
     }
+}
+
+// The same for a length known to the compiler (the plan of fft_plan, whose
+// twiddles the table holds): the elements of a butterfly are at one address plus
+// constants, stage by stage, with none of the index arithmetic above.
+template <int N, int S, int Ls, bool RICH, int LW, bool INV, typename T>
+__device__ __forceinline__ void wfft_exact_stages(cplx<T>* line, const cplx<T>* tw, int lane) {
+    constexpr FftDesc D = fft_plan(N, RICH, RICH);
+    if constexpr (S < D.nstages) {
+        constexpr int R = D.radix[S], NBF = N / R, MAXB = cdiv(NBF, LW);
+        constexpr bool RD = NBF % 8 == 0, WR = Ls % 8 == 0 || (Ls == 1 && 8 % R == 0);
+        cplx<T> v[MAXB][R];
+        int dst[MAXB];
+#pragma unroll
+        for (int i = 0; i < MAXB; ++i) {
+            const int j = lane + LW * i;
+            dst[i] = -1;
+            if (NBF % LW == 0 || j < NBF) {
+                int k = 0;
+                if constexpr ((Ls & (Ls - 1)) == 0) k = j & (Ls - 1);
+                else k = j - fdiv(j, 1.0f / (float)Ls) * Ls;
+                const int pj = pad(j);
+#pragma unroll
+                for (int t = 0; t < R; ++t) v[i][t] = line[RD ? pj + t * (NBF + NBF / 8) : pad(j + t * NBF)];
+                if constexpr (Ls > 1) {
+#pragma unroll
+                    for (int t = 1; t < R; ++t) {
+                        const cplx<T> w = tw[t * Ls + k - 1];
+                        v[i][t] = INV ? cmulc(v[i][t], w) : cmul(v[i][t], w);
+                    }
+                }
+                rbfly<R, INV, T>(v[i]);
+                dst[i] = (j - k) * R + k;
+            }
+        }
+        line_sync<LW>();
+#pragma unroll
+        for (int i = 0; i < MAXB; ++i) {
+            if (NBF % LW == 0 || dst[i] >= 0) {
+                const int pd = pad(dst[i]);
+#pragma unroll
+                for (int t = 0; t < R; ++t)
+                    line[WR ? pd + t * (Ls % 8 == 0 ? Ls + Ls / 8 : 1) : pad(dst[i] + t * Ls)] = v[i][t];
+            }
+        }
+        line_sync<LW>();
+        wfft_exact_stages<N, S + 1, Ls * R, RICH, LW, INV, T>(line, tw, lane);
+    }
+}
+template <int N, bool INV, typename T, bool RICH, int LW = 64>
+__device__ __forceinline__ void wfft_exact(cplx<T>* line, const cplx<T>* tw, int lane) {
+    wfft_exact_stages<N, 0, 1, RICH, LW, INV, T>(line, tw, lane);
 }
 
 // 512-point transform of one line by one wavefront: the radix plan of 512 is

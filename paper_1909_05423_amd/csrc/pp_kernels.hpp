@@ -26,6 +26,18 @@ constexpr int xdir_waves(int nx) { return nx <= 512 ? 1 : (nx <= 1024 ? 2 : 4); 
 constexpr int xdir_threads(int nx) { return 64 * kXGroups * xdir_waves(nx); }
 constexpr int kXLdsBytes = 96 * 1024;          // x-kernel LDS target (lines + twiddle tables), two workgroups per CU
 constexpr int kXLdsMax = 160 * 1024 - 1024;    // x-kernel LDS ceiling (one workgroup per CU)
+// Radix-9 stages in the x kernels of any length: in float, and in double where
+// the workgroup's size sets the registers anyway.  Elsewhere in double they take
+// 135 registers instead of 125 and a workgroup per CU with them (x forward of 128
+// x 324 x 162: 47 -> 52 us; float 200 x 288 x 486: 109 -> 103, inverse 97 -> 87).
+constexpr bool x_nine(bool dbl, int waves) { return !dbl || waves == 4; }
+// Exact-count (FULL) forms of the x kernels: rows of 64 or 128 times 4, 6 or 8
+// values that have an instantiation, one line per group of wavefronts, whole
+// blocks in y.  (None for four wavefronts per line: at 1024 threads the
+// prefetched rows spill, and the general form does not.)
+constexpr bool x_exact(int nx, int ny, int ty) {
+    return (nx == 256 || nx == 384 || nx == 512 || nx == 768 || nx == 1024) && ty == 2 * kXGroups && ny % ty == 0;
+}
 constexpr int kXVals = kEpt;                   // values per lane of one line (64 xdir_waves(nx) kXVals >= nx)
 constexpr int kMaxLine = 2048;                 // longest x or y line
 // x-direction kernels: a workgroup owns `ty` consecutive rows (y0 .. y0+ty-1)

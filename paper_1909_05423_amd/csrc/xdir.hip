@@ -139,7 +139,7 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool SPLIT = !std::is_same_v<T, Ts>;   // double arithmetic, float spectra + double slots
     constexpr int NTH = 64 * kXGroups * WPL, LW = 64 * WPL, NG = kXGroups;   // lanes per line; lines at a time
-    constexpr bool RECOMP = !FULL || WPL > 1;   // (see wfft)
+    constexpr bool NINE = x_nine(sizeof(T) == 8, WPL);
     constexpr int PAIRS = RMAX / 2;   // FULL: column writes per thread, slots * nlines == NTH * PAIRS
     const int nx = FULL ? LW * RMAX : a.nx;
     const int ny = a.ny, nz = a.nz, ty = FULL ? 2 * NG : a.ty, ldl = a.ldl;
@@ -485,11 +485,12 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
             }
         } else if (FULL || WPL > 1) {
             line_sync<LW>();
-            wfft<RMAX, false, T, RECOMP, LW>(lds + wave * ldl, a.fx, twl, lane, FULL || wave < nlines);
+            if constexpr (FULL) wfft_exact<LW * RMAX, false, T, true, LW>(lds + wave * ldl, twl, lane);
+            else wfft<RMAX, false, T, true, LW, NINE>(lds + wave * ldl, a.fx, twl, lane, wave < nlines);
         } else {
             for (int j = wave; j < nlines; j += NG) {
                 wave_lds_sync();
-                wfft<RMAX, false, T, RECOMP>(lds + j * ldl, a.fx, twl, lane);
+                wfft<RMAX, false, T, true, 64, NINE>(lds + j * ldl, a.fx, twl, lane);
             }
         }
         lds_barrier();
@@ -567,7 +568,7 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) void k_xinv(const cplx<T>* __r
     constexpr bool R512 = FULL && WPL == 1 && RMAX == 8 && sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NTH = 64 * kXGroups * WPL, LW = 64 * WPL, NG = kXGroups;   // lanes per line; lines at a time
-    constexpr bool RECOMP = !FULL || WPL > 1;   // (see wfft)
+    constexpr bool NINE = x_nine(sizeof(T) == 8, WPL);
     constexpr int PAIRS = RMAX / 2;    // (slot, row pair) gathers per thread: slots * nlines <= NTH * PAIRS
     const int nx = FULL ? LW * RMAX : a.nx;
     const int ny = a.ny, nz = a.nz, ty = FULL ? 2 * NG : a.ty, ldl = a.ldl;
@@ -734,10 +735,12 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) void k_xinv(const cplx<T>* __r
                     w512_second<true, T>(line, tw, lane);
                     w512_last<true, T>(line, tw, lane, vl);
                 } else {
-                    wfft<RMAX, true, T, RECOMP, LW>(line, a.fx, twl, lane, mine);
+                    wfft_exact<LW * RMAX, true, T, true, LW>(line, twl, lane);
                 }
+            } else if constexpr (FULL) {
+                wfft_exact<LW * RMAX, true, T, true, LW>(line, twl, lane);
             } else {
-                wfft<RMAX, true, T, RECOMP, LW>(line, a.fx, twl, lane, mine);
+                wfft<RMAX, true, T, true, LW, NINE>(line, a.fx, twl, lane, mine);
             }
             if (FULL) {
 #pragma unroll
@@ -887,13 +890,6 @@ template <typename A, typename B, typename T> static bool x_far(const XArgs<T>& 
 int x_blocks(int ny, int ty, int nz, int batch) { return ((ny + ty - 1) / ty) * nz * batch; }
 
 
-// Row blocks of the FULL shape: nx = 64 WPL RMAX, one line per group of
-// wavefronts, whole blocks in y.  (None for four wavefronts per line: at 1024
-// threads its prefetched rows spill, the general form does not.)
-template <int WPL, int RMAX, typename T> static bool x_full(const XArgs<T>& a) {
-    return a.nx == 64 * WPL * RMAX && a.ty == 2 * kXGroups && a.ny % a.ty == 0;
-}
-
 template <typename T, typename Tin, typename Ts, int WPL, int RMAX, bool FACES, bool RES = false>
 static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
                                     const FaceArgs<Tin>& fa, int* records, hipStream_t s) {
@@ -901,7 +897,7 @@ static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, 
     constexpr int threads = 64 * kXGroups * WPL;
     int resident = 1;
     if constexpr (WPL <= 2) {
-        if (x_full<WPL, RMAX>(a)) {
+        if (a.nx == 64 * WPL * RMAX && x_exact(a.nx, a.ny, a.ty)) {
             const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, false, resident, sizeof(T) == 8 && x_far<Tin, Ts>(a, batch));
@@ -968,7 +964,7 @@ static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, 
     constexpr int threads = 64 * kXGroups * WPL;
     int resident = 1;
     if constexpr (WPL <= 2) {
-        if (x_full<WPL, RMAX>(a)) {
+        if (a.nx == 64 * WPL * RMAX && x_exact(a.nx, a.ny, a.ty)) {
             const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, sizeof(T) == 4, resident, (sizeof(Tout) == 8 || MODE != XINV_STORE) && x_far<T, Tout>(a, batch));

@@ -337,7 +337,8 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
             }
         } else if (own || WPP > 1) {
             line_sync<LW>();
-            wfft<EPL, false, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
+            if constexpr (FULL) wfft_exact<NYMAX, false, Tf, false, LW>(line, twl, lane);
+            else wfft<EPL, false, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
             if (!own) {
             } else if (a.by != BC_P) {
                 for (int k = lane; k < half; k += LW) {
@@ -584,7 +585,8 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
 #pragma unroll
                 for (int t = 0; t < EPL; ++t) dst[lane + 64 * t] = cvt<Tout>(v[t]);
             } else {
-                wfft<EPL, true, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
+                if constexpr (FULL) wfft_exact<NYMAX, true, Tf, false, LW>(line, twl, lane);
+                else wfft<EPL, true, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
 #pragma unroll
                 for (int k = 0; k < EPL; ++k) {
                     const int y = lane + LW * k;
