@@ -107,10 +107,17 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
     constexpr int kSZ = NW / WPP;                // planes per chunk, each shared by WPP wavefronts
     constexpr int LW = 64 * WPP;                 // lanes per plane
     constexpr int EPL = NYMAX / LW;              // plane elements per lane
-    constexpr int OWN = NYMAX / NTH;             // z-recurrence entries per thread
+    constexpr int OWN = cdiv(NYMAX, NTH);        // z-recurrence entries per thread
+    constexpr bool ALL = FULL && NYMAX % NTH == 0;   // every thread owns OWN entries
     constexpr int LDY = ZpipeLds<Tf, NYMAX, kSZ>::LDY;
     constexpr bool RECOMP = WPP > 1;             // (see wfft)
-    static_assert(EPL == kSZ * OWN, "one prefetch buffer serves both directions");
+    // Stages known to the compiler in the exact-count forms, except the mixed
+    // march's on lines of 1024: its periodic-z kernel (370 bytes of spills) gave
+    // NaN with them at 16 x 1024 x 8, from a cause not found; the run-time stages
+    // are right on every shape tried.
+    constexpr bool EXACT = FULL && !(NYMAX == 1024 && WPP == 1);
+    constexpr int PRE = EPL > kSZ * OWN ? EPL : kSZ * OWN;   // one prefetch buffer serves both directions
+    static_assert(YFWD || EPL == kSZ * OWN, "right-hand sides held per entry");
     cplx<Tf>* work = L.work;
     cplx<Tf>* twl = L.twl;
     cplx<Tf>* mkl = L.mkl;
@@ -187,7 +194,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
 #pragma unroll
     for (int o = 0; o < OWN; ++o) {
         const int e = tid + NTH * o;
-        live[o] = FULL || e < ny;
+        live[o] = ALL || e < ny;
         ec[o] = live[o] ? e : 0;
         winf[o] = (side ? a.bwinf : (fresh ? a.fwinf : a.winf))[(size_t)m * ny + ec[o]];
         elen[o] = (side ? a.belen : (fresh ? a.felen : a.elen))[(size_t)m * ny + ec[o]];
@@ -235,7 +242,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
     };
     // upward prefetch (clamped to the last plane): YFWD, elements y = lane + 64 k
     // of plane zc + wave; otherwise the thread's own entries of planes zc .. zc+NW-1
-    cplx<T> pre[EPL];
+    cplx<T> pre[PRE];
     auto load_plane = [&](int zc) __attribute__((always_inline)) {
         if constexpr (YFWD) {
             const cplx<Tin>* src = icol + (ptrdiff_t)min(zc + wave, nz - 1) * izs;
@@ -337,7 +344,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
             }
         } else if (own || WPP > 1) {
             line_sync<LW>();
-            if constexpr (FULL) wfft_exact<NYMAX, false, Tf, false, LW>(line, twl, lane);
+            if constexpr (EXACT) wfft_exact<NYMAX, false, Tf, false, LW>(line, twl, lane);
             else wfft<EPL, false, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
             if (!own) {
             } else if (a.by != BC_P) {
@@ -585,7 +592,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
 #pragma unroll
                 for (int t = 0; t < EPL; ++t) dst[lane + 64 * t] = cvt<Tout>(v[t]);
             } else {
-                if constexpr (FULL) wfft_exact<NYMAX, true, Tf, false, LW>(line, twl, lane);
+                if constexpr (EXACT) wfft_exact<NYMAX, true, Tf, false, LW>(line, twl, lane);
                 else wfft<EPL, true, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
 #pragma unroll
                 for (int k = 0; k < EPL; ++k) {
@@ -864,6 +871,12 @@ hipError_t launch_mid(cplx<T>* S, const MidArgs<T>& a, int batch, hipStream_t s)
     // 1.12 ms at 384^3 x 4; in double the 8-wavefront form is as fast)
     if constexpr (sizeof(T) == 4) {
         if (a.ny == 384) return launch_pipe_any<T, 384, 6>(S, a, batch, s);
+    }
+    // double lines of 384 in whole chunks of eight planes: the exact-count form,
+    // two of the eight wavefronts without entries in the recurrences (384^3 x 4
+    // march 1.99 -> 1.62 ms; compiled for two workgroups per CU, 1.59 ms with spills)
+    if constexpr (sizeof(T) == 8) {
+        if (pipe_full(a, 384, 8)) return launch_pipe<T, 384, 8, true, 1>(S, a, batch, s);
     }
     if (a.ny <= 512) return launch_pipe_any<T, 512, 8>(S, a, batch, s);
     if constexpr (sizeof(T) == 4) {

@@ -75,3 +75,21 @@ def test_long_y_lines(shape, bc, dtype):
 def test_long_lines_faces_and_adjoint(shape, dtype):
     _check(shape, "DDNNDN", dtype, faces=True)
     _check(shape, "NNPPNN", dtype, adjoint=True)
+
+
+@pytest.mark.parametrize("bc", ["NNPPPP", "DDDDPP", "PPPPNN"])
+def test_refined_lines_of_1024_read_no_stale_workspace(bc):
+    """The mixed march on lines of 1024, periodic z among them, on a workspace
+    filled with NaN before the first solve."""
+    import torch
+    from paper_1909_05423_amd import Plan
+    from gpu_util import banner, rel_max, to_dev
+    for shape in [(16, 1024, 8), (16, 1024, 48)]:
+        banner(f"refined lines of 1024 {bc} {shape}")
+        h = (1.0 / shape[2], 1.0 / shape[1], 1.0 / shape[0])
+        f = np.random.default_rng(67).standard_normal(shape)
+        plan = Plan(shape, bc, h, dtype="f32_refined")
+        plan.workspace.fill_(255)
+        u = plan.solve(to_dev(f[None]))
+        torch.cuda.synchronize()
+        assert rel_max(u[0].cpu().numpy(), oracle.solve(f, bc, h, "mean")) < 1e-12, (bc, shape)
