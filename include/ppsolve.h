@@ -78,8 +78,7 @@ typedef enum {
 
 /* Limits (the plan call returns PP_ERR_SIZE beyond them):
  *   nx, ny      factor as 2^a 3^b and are at most 2048 (whole lines are held on
- *               chip; y lines up to 1024 take the pipelined z march, longer ones
- *               a slower general march);
+ *               chip);
  *   nz * batch  at most 65535 (launch grid of the refinement residual);
  *   periodic z  nz >= 3;
  *   PCR / CR-P  z not periodic (PP_ERR_BC), nz at most 4096 and ny at most 512
@@ -130,7 +129,13 @@ typedef enum { PP_ZSOLVER_THOMAS = 0, PP_ZSOLVER_PCR = 1, PP_ZSOLVER_CR = 2 } pp
 pp_status pp_plan_set_zsolver(pp_plan p, pp_zsolver solver);
 
 /* Layout of the Thomas march (PP_ZSOLVER_THOMAS; the other solvers ignore it).
- *   PP_ZSPLIT_AUTO  default: split where the columns (x-wavenumber slots times
+ *   PP_ZSPLIT_AUTO  default.  PP_F64 and PP_F32 plans whose planes fit on chip
+ *                   (lines up to 256; 128 x 128 in double, twice that in
+ *                   float; float plans also need the bound on near-singular
+ *                   systems below) take whole planes per workgroup and the
+ *                   z-systems in one pass instead of the march, and plans
+ *                   whose march cannot be split and has few columns the
+ *                   z-systems in one pass.  Otherwise split where the columns (x-wavenumber slots times
  *                   batch) are at most 1/2 (PP_F64), 2 (PP_F32) or 4
  *                   (PP_F32_REFINED) per compute unit of the device, or, in
  *                   PP_F64 on y lines up to 512 with more columns than
