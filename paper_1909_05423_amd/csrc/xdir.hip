@@ -114,10 +114,8 @@ template <typename T> __device__ __forceinline__ void put_spec(cplx<T>* p, const
 // Minimum waves per SIMD the compiler must leave room for.  2 for the
 // all-float forward kernel on rows up to 512 and for the double kernel on
 // rows of 512 without face values (4 registers over the budget of two waves);
-// no constraint elsewhere: the kernels with double data, and the float kernel
-// on rows of 1024, spill under it (the float one 104 registers, 3.0 ms at
-// 1024 x 1024 x 512; unconstrained it takes AGPRs instead, one wave per SIMD,
-// 1.75 ms).  The general form of the fused residual (RES) spills under it too.
+// no constraint elsewhere: the other kernels with double data spill under it,
+// the general form of the fused residual (RES) among them.
 // Lines shared by wavefronts: the workgroup's own wavefronts per SIMD.
 template <typename T, typename Tin, int WPL, int RMAX, bool FACES, bool FULL = true, bool RES = false>
 constexpr int kXfwdMinWaves =
