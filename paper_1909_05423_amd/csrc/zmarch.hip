@@ -111,11 +111,6 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
     constexpr bool ALL = FULL && NYMAX % NTH == 0;   // every thread owns OWN entries
     constexpr int LDY = ZpipeLds<Tf, NYMAX, kSZ>::LDY;
     constexpr bool RECOMP = WPP > 1;             // (see wfft)
-    // Stages known to the compiler in the exact-count forms, except the mixed
-    // march's on lines of 1024: its periodic-z kernel (370 bytes of spills) gave
-    // NaN with them at 16 x 1024 x 8, from a cause not found; the run-time stages
-    // are right on every shape tried.
-    constexpr bool EXACT = FULL && !(NYMAX == 1024 && WPP == 1);
     constexpr int PRE = EPL > kSZ * OWN ? EPL : kSZ * OWN;   // one prefetch buffer serves both directions
     static_assert(YFWD || EPL == kSZ * OWN, "right-hand sides held per entry");
     cplx<Tf>* work = L.work;
@@ -147,9 +142,18 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) / WPP);   // plane of the chunk
     const int lane = WPP == 1 ? (tid & 63) : tid - wave * LW;            // among the plane's lanes
-    for (int i = tid; i < ny; i += NTH) {
-        twl[i] = af.twy[i];
-        mkl[i] = af.mky[i];
+    // (A loop that every lane takes equally often.  Past a loop that lanes leave
+    // one by one no lane is active until the execution mask is restored, and the
+    // compiler may place a register's spill before that: it then stores nothing.
+    // The mixed march on lines of 1024 lost its thread offset so and stored to
+    // addresses made of what the stack held; tests/test_device_code.py looks for
+    // such stores in the built kernels.)
+    for (int i0 = 0; i0 < ny; i0 += NTH) {
+        const int i = i0 + tid;
+        if (ALL || i < ny) {
+            twl[i] = af.twy[i];
+            mkl[i] = af.mky[i];
+        }
     }
     // periodic y on lines of 512: the transforms take their first (forward) or
     // last (inverse) stage in registers (w512_*)
@@ -344,7 +348,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
             }
         } else if (own || WPP > 1) {
             line_sync<LW>();
-            if constexpr (EXACT) wfft_exact<NYMAX, false, Tf, false, LW>(line, twl, lane);
+            if constexpr (FULL) wfft_exact<NYMAX, false, Tf, false, LW>(line, twl, lane);
             else wfft<EPL, false, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
             if (!own) {
             } else if (a.by != BC_P) {
@@ -592,7 +596,7 @@ __device__ __forceinline__ void zpipe_body(const cplx<Tin>* icol, ptrdiff_t izs,
 #pragma unroll
                 for (int t = 0; t < EPL; ++t) dst[lane + 64 * t] = cvt<Tout>(v[t]);
             } else {
-                if constexpr (EXACT) wfft_exact<NYMAX, true, Tf, false, LW>(line, twl, lane);
+                if constexpr (FULL) wfft_exact<NYMAX, true, Tf, false, LW>(line, twl, lane);
                 else wfft<EPL, true, Tf, RECOMP, LW>(line, af.fy, twl, lane, own);
 #pragma unroll
                 for (int k = 0; k < EPL; ++k) {
