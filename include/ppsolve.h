@@ -70,7 +70,8 @@ typedef enum {
     PP_ERR_WORKSPACE = -5,     /* workspace pointer null or misaligned (256 B) */
     PP_ERR_HIP = -6,           /* a HIP call failed (launch, copy, synchronisation) */
     PP_ERR_NOT_CONVERGED = -7, /* refinement did not reach its tolerance in max_iter steps */
-    PP_ERR_NONFINITE = -8,     /* the source held an Inf or NaN (reported where the
+    PP_ERR_NONFINITE = -8,     /* the source held an Inf or NaN, or the refined solve
+                                  went past the float range (reported where the
                                   library reads scalars back: refinement, last_info) */
     PP_ERR_SCRATCH = -9        /* pp_solve_noalloc: the plan needs more workspace than
                                   PP_NOALLOC_SCRATCH_BYTES */

@@ -66,7 +66,9 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize_update(const double* _
         }
     }
     if (threadIdx.x == 0) {
-        const double rel = (gu == 0.0) ? 0.0 : gd / gu;   // NaN stays NaN
+        // a NaN among the corrections is in gd alone: gu, taken by fmax over u,
+        // drops it and is 0 where all of u is NaN
+        const double rel = gd != gd ? gd : (gu == 0.0 ? 0.0 : gd / gu);
         sc[SC_RELPREV] = first ? 1.0 : sc[SC_REL];
         sc[SC_MAXD] = gd;
         sc[SC_MAXU] = gu;
