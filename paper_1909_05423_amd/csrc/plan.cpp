@@ -1472,9 +1472,9 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
     }
     p->ty = 2 * lines;
     if (pp::x_exact(nx, ny, p->ty)) p->fx = pp::fft_plan(nx, true, true);
-    // partial records per batch entry: one per (workgroup, wavefront) of the persistent
-    // x kernels, whose grid never exceeds the row blocks of all batch entries
-    p->nper = (size_t)((ny + p->ty - 1) / p->ty) * nz * batch * pp::kXGroups * pp::xdir_waves(nx);
+    // partial records per batch entry: one per (workgroup, group of wavefronts) of the
+    // persistent x kernels, whose grid never exceeds the row blocks of all batch entries
+    p->nper = (size_t)std::min(pp::x_blocks(ny, p->ty, nz, batch), pp::kXGridMax) * pp::kXGroups;
     // split march: the meeting point on a chunk boundary near the middle (the
     // refined solve's march has the float march's chunks)
     {
@@ -1530,7 +1530,8 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
     p->o_scalars = off;
     off = align_up(off + sizeof(double) * (pp::SC_COUNT + 4 * (size_t)batch));
     p->o_partial = off;
-    off = align_up(off + sizeof(double) * 3 * p->nper * batch);
+    // (the plane kernels write one sum per plane there)
+    off = align_up(off + sizeof(double) * std::max(3 * p->nper, (size_t)nz) * batch);
     for (int i = 0; i < p->ntab; ++i) {
         p->o_tab[i] = off;
         off = align_up(off + p->tb[i].blob.size());

@@ -24,6 +24,7 @@ constexpr int kEpt = 8;
 constexpr int kXGroups = 4;
 constexpr int xdir_waves(int nx) { return nx <= 512 ? 1 : (nx <= 1024 ? 2 : 4); }
 constexpr int xdir_threads(int nx) { return 64 * kXGroups * xdir_waves(nx); }
+constexpr int kXGridMax = 1024;                // largest grid of an x kernel: four workgroups for each of 256 CUs
 constexpr int kXLdsBytes = 96 * 1024;          // x-kernel LDS target (lines + twiddle tables), two workgroups per CU
 constexpr int kXLdsMax = 160 * 1024 - 1024;    // x-kernel LDS ceiling (one workgroup per CU)
 // Radix-9 stages in the x kernels of any length: in float, and in double where
@@ -225,8 +226,9 @@ struct ResidualArgs {
 
 // --- launchers (return hipError_t of the launch) -----------------------------
 // Row blocks of the x kernels.  They run on a persistent grid (never larger than
-// the row blocks) and write one partial record per (batch entry, workgroup,
-// wavefront): the launchers return the records per batch entry.
+// the row blocks, nor than kXGridMax) and write one partial record per (batch
+// entry, workgroup, group of wavefronts sharing a line): the launchers return the
+// records per batch entry.
 int x_blocks(int ny, int ty, int nz, int batch);
 
 // faces: null, or the face values to lift into the source as it is read.

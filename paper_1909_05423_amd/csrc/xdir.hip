@@ -23,6 +23,7 @@
 // Writing columns with y contiguous is the x <-> y transpose, done through LDS
 // so that both the row reads and the column writes are coalesced.
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <set>
@@ -87,6 +88,26 @@ __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v = nmax(v, __shfl_down(v, off, 64));
     return v;
+}
+
+// v[0] summed, the others' maxima taken over the WPL wavefronts of each group,
+// into its first; every thread of the workgroup takes part.
+template <int WPL, int N> __device__ __forceinline__ void group_combine(double (&v)[N], double* red, int tid) {
+    const int w = tid >> 6;
+    if ((tid & 63) == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) red[N * w + i] = v[i];
+    }
+    lds_barrier();
+    if (w % WPL == 0) {
+#pragma unroll
+        for (int q = 1; q < WPL; ++q) {
+            v[0] += red[N * (w + q)];
+#pragma unroll
+            for (int i = 1; i < N; ++i) v[i] = nmax(v[i], red[N * (w + q) + i]);
+        }
+    }
+    lds_barrier();   // read before they are written again
 }
 
 // Store of one spectral value by the forward x kernel.  Float spectra are
@@ -275,15 +296,13 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
             return 0.0;
         }
     };
-    // per-wavefront sums of the source, one record per (batch entry, workgroup, wavefront)
+    // sums of the source, one record per (batch entry, workgroup, group of wavefronts)
     const int batch = (int)(nblocks / ((size_t)nyb * nz));
-    constexpr int NW = NTH / 64;
-    const int wid = tid >> 6;
-    const bool lead = (tid & 63) == 0;
-    const size_t rec_per_batch = (size_t)gridDim.x * NW;
-    if (lead) {
+    __shared__ double red[2 * WPL * NG];   // (lines shared by wavefronts only)
+    const size_t rec_per_batch = (size_t)gridDim.x * NG;
+    if (lane == 0) {
         for (int bb = 0; bb < batch; ++bb) {
-            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NW + wid;
+            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NG + wave;
             partial[2 * rec] = 0.0;
             partial[2 * rec + 1] = 0.0;
         }
@@ -294,11 +313,12 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
     double rscale = 1.0;
     if constexpr (RES) rscale = a.sc[SC_SCALE];
     auto flush = [&]() {
-        const double s_ = wave_sum(acc) * rscale, m_ = wave_max(amax) * rscale;
-        if (lead && cur_b >= 0) {
-            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NW + wid;
-            partial[2 * rec] = s_;
-            partial[2 * rec + 1] = m_;
+        double v[2] = {wave_sum(acc) * rscale, wave_max(amax) * rscale};
+        if constexpr (WPL > 1) group_combine<WPL, 2>(v, red, tid);
+        if (lane == 0 && cur_b >= 0) {
+            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NG + wave;
+            partial[2 * rec] = v[0];
+            partial[2 * rec + 1] = v[1];
         }
         acc = 0.0;
         amax = 0.0;
@@ -551,7 +571,7 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
 // transform and the row writes are per wavefront.
 // MODE XINV_STORE writes u = x - shift[b]; XINV_UPDATE adds the scaled
 // correction to a double u and XINV_FIRST stores it without reading u; both
-// write per-wavefront partials (sum over the gauge region, max |d|, max |u|).
+// write partials per group of wavefronts (sum over the gauge region, max |d|, max |u|).
 // Tp: type of the previous solution an update adds to (Tout: u itself, in
 // place; float: the separate array uprev holding the first float solution).
 template <typename T, typename Tout, typename Tp, int WPL, int MODE, int RMAX, bool FULL>
@@ -588,14 +608,12 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) void k_xinv(const cplx<T>* __r
     double inv_scale = 1.0;
     if (UPD) inv_scale = scalars[SC_INVSCALE];
 
-    // refinement partials, one record per (batch entry, workgroup, wavefront)
-    constexpr int NW = NTH / 64;
-    const int wid = tid >> 6;
-    const bool lead = (tid & 63) == 0;
-    const size_t rec_per_batch = (size_t)gridDim.x * NW;
-    if (UPD && lead) {
+    // refinement partials, one record per (batch entry, workgroup, group of wavefronts)
+    __shared__ double red[3 * WPL * NG];   // (lines shared by wavefronts only)
+    const size_t rec_per_batch = (size_t)gridDim.x * NG;
+    if (UPD && lane == 0) {
         for (int bb = 0; bb < batch; ++bb) {
-            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NW + wid;
+            const size_t rec = bb * rec_per_batch + (size_t)blockIdx.x * NG + wave;
             partial[3 * rec] = 0.0;
             partial[3 * rec + 1] = 0.0;
             partial[3 * rec + 2] = 0.0;
@@ -609,12 +627,13 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) void k_xinv(const cplx<T>* __r
     auto flush = [&]() {
         if (!UPD) return;
         if (chk != chk) dmax = chk;
-        const double s_ = wave_sum(acc), d_ = wave_max(dmax), u_ = wave_max(umax);
-        if (lead && cur_b >= 0) {
-            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NW + wid;
-            partial[3 * rec] = s_;
-            partial[3 * rec + 1] = d_;
-            partial[3 * rec + 2] = u_;
+        double v[3] = {wave_sum(acc), wave_max(dmax), wave_max(umax)};
+        if constexpr (WPL > 1) group_combine<WPL, 3>(v, red, tid);
+        if (lane == 0 && cur_b >= 0) {
+            const size_t rec = cur_b * rec_per_batch + (size_t)blockIdx.x * NG + wave;
+            partial[3 * rec] = v[0];
+            partial[3 * rec + 1] = v[1];
+            partial[3 * rec + 2] = v[2];
         }
         acc = 0.0;
         dmax = 0.0;
@@ -875,7 +894,7 @@ template <auto K> static hipError_t x_resident(int threads, size_t lds, int* out
 static int x_grid(int nblocks, bool paired, int resident, bool two) {
     const int per = two ? 2 : (resident >= 3 ? (resident < 4 ? resident : 4) : 2 * resident);
     const int work = paired ? (nblocks + 1) / 2 : nblocks;
-    const int most = device_cus() * per;
+    const int most = std::min(device_cus() * per, kXGridMax);
     return work < most ? work : most;
 }
 // Source and spectra of a launch past the last-level cache.
@@ -899,7 +918,7 @@ static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, 
             const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, false, resident, sizeof(T) == 8 && x_far<Tin, Ts>(a, batch));
-            *records = grid * kXGroups * WPL;
+            *records = grid * kXGroups;
             hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>),
                                dim3(grid), dim3(threads), x_lds_bytes(a), s, f, S, partial, a,
                                nb, fa);
@@ -910,7 +929,7 @@ static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, 
         const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, false, resident, false);
-            *records = grid * kXGroups * WPL;
+            *records = grid * kXGroups;
         hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>), dim3(grid),
                            dim3(threads), x_lds_bytes(a), s, f, S, partial, a, nb, fa);
     }
@@ -966,7 +985,7 @@ static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, 
             const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, sizeof(T) == 4, resident, (sizeof(Tout) == 8 || MODE != XINV_STORE) && x_far<T, Tout>(a, batch));
-            if (records) *records = grid * kXGroups * WPL;
+            if (records) *records = grid * kXGroups;
             hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>),
                                dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u,
                                uprev, a, shift, scalars, gauge_region, partial, nb);
@@ -977,7 +996,7 @@ static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, 
         const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, sizeof(T) == 4, resident, false);
-            if (records) *records = grid * kXGroups * WPL;
+            if (records) *records = grid * kXGroups;
         hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>),
                            dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u, uprev,
                            a, shift, scalars, gauge_region, partial, nb);
