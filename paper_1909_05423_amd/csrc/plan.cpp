@@ -33,6 +33,7 @@ struct Tables {
     size_t t_twx = 0, t_mkx = 0, t_twy = 0, t_mky = 0, t_rowoff = 0, t_winf = 0, t_wlast = 0, t_wrows = 0;
     size_t t_elen = 0;
     size_t t_twxp = 0, t_twyp = 0;   // twiddles of the plane kernels' radices
+    size_t t_winfl = 0, t_wlastl = 0, t_wrowsl = 0;   // low parts of winf, wlast, wrows (pivots_low)
     size_t t_bmid = 0;   // interior z diagonal per (slot, entry, part)
     // split march: the lower half's pivots (by distance from the bottom row) and the meeting rows
     size_t t_browoff = 0, t_belen = 0, t_bwinf = 0, t_bwrows = 0, t_meet = 0;
@@ -84,6 +85,7 @@ struct pp_plan_s {
     // the lowest wavenumbers of long columns with Neumann or periodic x, y)
     // make it large, and the automatic choice then keeps one march per column
     double split_gmax = 0.0;
+    bool pivots_low = false;   // float plans of the plane kernels whose march would be split: pivots in two floats
     bool plane_ok = false;   // a plane fits the one-workgroup transforms (plane.hip)
     bool lines_ok = false;   // else: y lines fit the separate y transforms
     // refined solve: slots lo0 .. lo0+nlo-1 kept in double by the x transform and the z march
@@ -260,6 +262,8 @@ template <typename T> struct Line {
     std::vector<T> body;
     T winf = 0, wlast = 0;
     int tail = 0;
+    std::vector<T> bodyl;           // what rounding to T took off the pivots (not periodic z)
+    T winfl = 0, wlastl = 0;
     std::vector<T> alpha, qp;       // periodic z only
     T qlast = 0, inv_den = 0, inv_gamma = 0;
 };
@@ -299,10 +303,13 @@ template <typename T> void periodic_extras(double bmid, int nz, const std::vecto
 }
 
 // krow >= 0: *wk = the reciprocal pivot of row krow in double (krow <= nz - 2;
-// the upper half's last row in a split march).
+// the upper half's last row in a split march).  low: the body runs on until the
+// pivots are within 2^-30 of the converged one (stopping at equal floats, the low
+// parts past the table would be those of other rows: 1.5e-6 of the solution
+// instead of 3e-9 at 2048 rows, lambda h^2 = 1e-5).
 template <typename T>
 void pivots(double lam, int nz, double hz, int bz0, int bz1, bool pinned, Line<T>* out, int krow = -1,
-            double* wk = nullptr) {
+            double* wk = nullptr, bool low = false) {
     const double bmid = -2.0 + hz * hz * lam;
     out->alpha.clear();
     out->qp.clear();
@@ -329,7 +336,9 @@ void pivots(double lam, int nz, double hz, int bz0, int bz1, bool pinned, Line<T
     const double d1 = (bz1 == pp::BC_P) ? 0.0 : (bz1 == pp::BC_D) ? -1.0 : 1.0;
     out->body.clear();
     if (nz == 1) {
-        out->wlast = pinned ? T(0) : (T)(1.0 / (bmid + d0 + d1));
+        const double only = pinned ? 0.0 : 1.0 / (bmid + d0 + d1);
+        out->wlast = (T)only;
+        out->wlastl = (T)(only - (double)out->wlast);
         out->winf = 0;
         out->tail = 0;
         return;
@@ -346,13 +355,21 @@ void pivots(double lam, int nz, double hz, int bz0, int bz1, bool pinned, Line<T
     }
     const double wend = seq.back();  // value at index nz-2
     if (krow >= 0 && wk) *wk = seq[std::min((size_t)krow, seq.size() - 1)];
-    out->wlast = (T)(1.0 / ((bmid + d1) - wend));
+    const double wl = 1.0 / ((bmid + d1) - wend);
+    out->wlast = (T)wl;
+    out->wlastl = (T)(wl - (double)out->wlast);
     out->winf = (T)wend;
+    out->winfl = (T)(wend - (double)out->winf);
     int L = (int)seq.size();
-    while (L > 0 && (T)seq[L - 1] == out->winf) --L;
+    while (L > 0 && (T)seq[L - 1] == out->winf && (!low || std::fabs(seq[L - 1] - wend) <= 0x1p-30 * std::fabs(wend)))
+        --L;
     out->tail = L;
     out->body.resize(L);
-    for (int i = 0; i < L; ++i) out->body[i] = (T)seq[i];
+    out->bodyl.resize(L);
+    for (int i = 0; i < L; ++i) {
+        out->body[i] = (T)seq[i];
+        out->bodyl[i] = (T)(seq[i] - (double)out->body[i]);
+    }
 }
 
 // The lower half of a split march eliminates upward from the bottom face: the
@@ -549,7 +566,8 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
                     ln.tail = 0;
                 } else {
                     const bool pinned = p->singular && m == 0 && e == 0 && part == 0;
-                    pivots<T>(lamx[kx] + lamy[ky], nz, p->h[2], p->bz0, p->bz1, pinned, &ln, ks - 1, &wk);
+                    pivots<T>(lamx[kx] + lamy[ky], nz, p->h[2], p->bz0, p->bz1, pinned, &ln, ks - 1, &wk,
+                              p->pivots_low);
                 }
                 if (nseg > 0) {
                     if (slines[m].empty()) slines[m].resize((size_t)ny * 2);
@@ -607,6 +625,26 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
                 }
             }
         }
+    }
+    if (p->pivots_low) {
+        std::vector<T> low((size_t)slots * ny * 2), lastl(low.size());
+        for (int m = 0; m < slots; ++m)
+            for (int e = 0; e < 2 * ny; ++e) {
+                low[(size_t)m * ny * 2 + e] = lines[m][e].winfl;
+                lastl[(size_t)m * ny * 2 + e] = lines[m][e].wlastl;
+            }
+        tb.t_winfl = em.put(sizeof(T) * low.size());
+        std::memcpy(tb.blob.data() + tb.t_winfl, low.data(), sizeof(T) * low.size());
+        tb.t_wlastl = em.put(sizeof(T) * lastl.size());
+        std::memcpy(tb.blob.data() + tb.t_wlastl, lastl.data(), sizeof(T) * lastl.size());
+        tb.t_wrowsl = em.put(sizeof(T) * 2 * std::max<size_t>(rows, 1) * ny);
+        T* wl = reinterpret_cast<T*>(tb.blob.data() + tb.t_wrowsl);
+        for (int m = 0; m < slots; ++m)
+            for (int z = 0; z < lmax[m]; ++z)
+                for (int e = 0; e < 2 * ny; ++e) {
+                    const Line<T>& ln = lines[m][e];
+                    wl[(size_t)(rowoff[m] + z) * ny * 2 + e] = (z < ln.tail) ? ln.bodyl[z] : ln.winfl;
+                }
     }
     if (ks > 0) {
         // the lower half's tables, laid out as the upper half's
@@ -901,6 +939,11 @@ pp::MidArgs<T> make_midargs(pp_plan p, unsigned char* ws, bool project, bool dem
     a.wrows = reinterpret_cast<const cplx<T>*>(t + tb.t_wrows);
     a.winf = reinterpret_cast<const cplx<T>*>(t + tb.t_winf);
     a.wlast = reinterpret_cast<const cplx<T>*>(t + tb.t_wlast);
+    if (p->pivots_low) {
+        a.winfl = reinterpret_cast<const cplx<T>*>(t + tb.t_winfl);
+        a.wlastl = reinterpret_cast<const cplx<T>*>(t + tb.t_wlastl);
+        a.wrowsl = reinterpret_cast<const cplx<T>*>(t + tb.t_wrowsl);
+    }
     // the split march where the columns alone would leave half the compute
     // units or more without a workgroup
     // automatic, by columns (slots x batch) per compute unit, as measured:
@@ -1054,6 +1097,8 @@ template <typename T> pp::PlaneArgs<T> make_planeargs(pp_plan p, unsigned char* 
 // Float plans with a nearly singular z-system (see split_gmax) keep the two-way
 // split: two short recurrences round less than one long one, which the pass
 // over segments is (2047 x 32 x 96 PP PP DN: 4.4e-7 split, 1.7e-6 in one pass).
+// Other float plans that the march would split take their pivots in two floats
+// and the recurrences in double (k_zscan).
 bool use_planes(pp_plan p) {
     return p->plane_ok && p->zsolver == 0 && p->zsplit_mode == PP_ZSPLIT_AUTO &&
            (p->dtype == PP_F64 || p->split_gmax <= kSplitGMax);
@@ -1517,6 +1562,9 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
         p->lines_ok = true;
         p->fyp = plane_radices(ny, true);
     }
+    // (periodic z and columns too short to split had one recurrence over the
+    // whole column, which the one pass rounds like)
+    p->pivots_low = dtype == PP_F32 && p->plane_ok && p->zsplit > 0;
     if (f64) build_tables<double>(p, p->tb[0]);
     else build_tables<float>(p, p->tb[0]);
     if (dtype == PP_F32_REFINED) {
@@ -1525,39 +1573,55 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
         set_mixed_slots(p);
     }
 
-    const size_t n = (size_t)nx * ny * nz;
-    size_t off = 0;
-    p->o_scalars = off;
-    off = align_up(off + sizeof(double) * (pp::SC_COUNT + 4 * (size_t)batch));
-    p->o_partial = off;
-    // (the plane kernels write one sum per plane there)
-    off = align_up(off + sizeof(double) * std::max(3 * p->nper, (size_t)nz) * batch);
-    for (int i = 0; i < p->ntab; ++i) {
-        p->o_tab[i] = off;
-        off = align_up(off + p->tb[i].blob.size());
-    }
-    p->o_S = off;
-    off = align_up(off + p->elem * (size_t)batch * p->slots * nz * ny);
-    p->o_r = off;   // refined, rows over 512: the double residual
-    if (dtype == PP_F32_REFINED && !pp::res_fused_supported(nx)) off = align_up(off + sizeof(double) * n * batch);
-    p->o_u0 = off;
-    if (dtype == PP_F32_REFINED) off = align_up(off + sizeof(float) * n * batch);
-    p->o_lo = off;
-    off = align_up(off + sizeof(cplx<double>) * (size_t)batch * p->nlo * nz * ny);
-    if (p->zsegs > 0) {
-        // segment end values (2 per segment) and couplings (2 per segment),
-        // per (batch, slot, entry)
-        p->o_seg = off;
-        off = align_up(off + p->elem * (size_t)batch * p->slots * ny * p->zsegs * 4);
-    }
-    if (p->zsplit > 0) {
+    auto lay_out = [&]() -> size_t {
+        const size_t n = (size_t)nx * ny * nz;
+        size_t off = 0;
+        p->o_scalars = off;
+        off = align_up(off + sizeof(double) * (pp::SC_COUNT + 4 * (size_t)batch));
+        p->o_partial = off;
+        // (the plane kernels write one sum per plane there)
+        off = align_up(off + sizeof(double) * std::max(3 * p->nper, (size_t)nz) * batch);
         for (int i = 0; i < p->ntab; ++i) {
-            p->o_zb[i] = off;
-            const size_t el = (i == 0) ? p->elem : sizeof(cplx<double>);
-            off = align_up(off + el * (size_t)batch * p->slots * 2 * ny);
+            p->o_tab[i] = off;
+            off = align_up(off + p->tb[i].blob.size());
+        }
+        p->o_S = off;
+        off = align_up(off + p->elem * (size_t)batch * p->slots * nz * ny);
+        p->o_r = off;   // refined, rows over 512: the double residual
+        if (dtype == PP_F32_REFINED && !pp::res_fused_supported(nx)) off = align_up(off + sizeof(double) * n * batch);
+        p->o_u0 = off;
+        if (dtype == PP_F32_REFINED) off = align_up(off + sizeof(float) * n * batch);
+        p->o_lo = off;
+        off = align_up(off + sizeof(cplx<double>) * (size_t)batch * p->nlo * nz * ny);
+        if (p->zsegs > 0) {
+            // segment end values (2 per segment) and couplings (2 per segment),
+            // per (batch, slot, entry)
+            p->o_seg = off;
+            off = align_up(off + p->elem * (size_t)batch * p->slots * ny * p->zsegs * 4);
+        }
+        if (p->zsplit > 0) {
+            for (int i = 0; i < p->ntab; ++i) {
+                p->o_zb[i] = off;
+                const size_t el = (i == 0) ? p->elem : sizeof(cplx<double>);
+                off = align_up(off + el * (size_t)batch * p->slots * 2 * ny);
+            }
+        }
+        return off;
+    };
+    p->ws_bytes = lay_out();
+    if (p->pivots_low && p->ws_bytes > pp::kScratchBytes) {
+        // a plan that fits the fixed workspace of pp_solve_noalloc but for the
+        // low parts of its pivots keeps to it, and to the march
+        const Tables& tb = p->tb[0];
+        const size_t low = align_up(tb.t_wrowsl + sizeof(float) * 2 * std::max<size_t>(tb.table_rows, 1) * ny) - tb.t_winfl;
+        if (p->ws_bytes - low <= pp::kScratchBytes) {
+            p->pivots_low = false;
+            p->plane_ok = false;
+            p->tb[0] = Tables{};
+            build_tables<float>(p, p->tb[0]);
+            p->ws_bytes = lay_out();
         }
     }
-    p->ws_bytes = off;
     *out = p;
     return PP_OK;
 }

@@ -521,8 +521,19 @@ __global__ __launch_bounds__(NTH) void k_ylines(cplx<T>* __restrict__ S, LineArg
 // y give the Sherman-Morrison factor before the sweep back, which then starts
 // from y - c qp.
 // ---------------------------------------------------------------------------
-template <typename T, int L, bool PERZ, bool ONE>
-__global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S, MidArgs<T> a, ScanArgs g) {
+//
+// Float spectra whose march would be split (Ts float, T double): one recurrence
+// over the whole column in float carries its rounding, and that of the float
+// pivots, which is the same in every row past their table, further than the
+// pieces of a split or segmented march do.  There the pivots are in two floats
+// (MidArgs::wrowsl) and the recurrences in double, which leaves the rounding of
+// the spectra themselves (rms error from the f64 solve, one float recurrence, the
+// split march and this: 1000 x 128 x 64 DDDDDN x 16 1.2e-6, 5.2e-7, 4.6e-7; 2048
+// x 32 x 128 x 6 2.0e-6, 8.1e-7, 5.5e-7; 64 x 64 x 64 x 16 gradient 104 -> 111 us).
+template <typename Ts, typename T, int L, bool PERZ, bool ONE>
+__global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<Ts>* __restrict__ S, MidArgs<Ts> a, ScanArgs g) {
+    constexpr bool LOW = !std::is_same_v<Ts, T>;
+    static_assert(!(LOW && PERZ), "periodic z is never split");
     extern __shared__ __align__(16) unsigned char smem[];
     const int ct = 1 << g.lct, P = g.segs, ny = a.ny, nz = a.nz;
     cplx<T>* sA = reinterpret_cast<cplx<T>*>(smem);   // a value per (wavefront, column) each
@@ -535,7 +546,7 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     const bool on = seg < P && c < a.slots * ny;
     const int cc = on ? c : 0;
     const int m = cc / ny, e = cc - m * ny;
-    cplx<T>* col = S + (size_t)b * a.slots * nz * ny + (size_t)m * a.sstride + e;
+    cplx<Ts>* col = S + (size_t)b * a.slots * nz * ny + (size_t)m * a.sstride + e;
     const size_t zs = (size_t)a.zstride;
     const bool sing = a.singular && c == 0;
     const cplx<T> zero = mk<T>(T(0), T(0));
@@ -546,14 +557,18 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     auto rows = [&](int z0) __attribute__((always_inline)) {
         const int zb = z0 + seg * L;
 #pragma unroll
-        for (int r = 0; r < L; ++r) y[r] = col[(size_t)(zb + r < nz ? zb + r : nz - 1) * zs];
+        for (int r = 0; r < L; ++r) y[r] = cvt<T>(col[(size_t)(zb + r < nz ? zb + r : nz - 1) * zs]);
     };
     rows(0);
     cplx<T> winf = zero, wlast = zero;
     int elen = 0, roff = 0;
     if (on) {
-        winf = a.winf[(size_t)m * ny + e];
-        wlast = a.wlast[(size_t)m * ny + e];
+        winf = cvt<T>(a.winf[(size_t)m * ny + e]);
+        wlast = cvt<T>(a.wlast[(size_t)m * ny + e]);
+        if constexpr (LOW) {
+            winf = cadd(winf, cvt<T>(a.winfl[(size_t)m * ny + e]));
+            wlast = cadd(wlast, cvt<T>(a.wlastl[(size_t)m * ny + e]));
+        }
         elen = a.elen[(size_t)m * ny + e];
         roff = a.rowoff[m];
     }
@@ -565,9 +580,9 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
             qlen = a.qelen[(size_t)m * ny + e];
             aoff = a.aoff[m];
             qoff = a.qoff[m];
-            qlast = a.qlast[(size_t)m * ny + e];
-            ig = a.inv_gamma[(size_t)m * ny + e];
-            id = a.inv_den[(size_t)m * ny + e];
+            qlast = cvt<T>(a.qlast[(size_t)m * ny + e]);
+            ig = cvt<T>(a.inv_gamma[(size_t)m * ny + e]);
+            id = cvt<T>(a.inv_den[(size_t)m * ny + e]);
         }
     }
 
@@ -594,19 +609,24 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
         lds_barrier();
     }
 
-    // Eight rows from zb of a table that holds `len` of them from row `off`; past
-    // them the value `past`.  One branch for the eight (skipped by a wavefront
+    // Eight rows from zb of a table that holds `len` of them from row `off` (`low`:
+    // their low parts, or null); past them the value `past`.  One branch for the eight (skipped by a wavefront
     // whose columns have none left): a branch per row waits for each load by
     // itself (200 x 192 x 256 f32 periodic: 45 -> 31 us).
     constexpr int H = 8;
     static_assert(L % H == 0, "rows in groups of eight");
-    auto table = [&](const cplx<T>* rows_, int off, int len, int zb, cplx<T> past, cplx<T>* t) __attribute__((always_inline)) {
+    auto table = [&](const cplx<Ts>* rows_, const cplx<Ts>* low, int off, int len, int zb, cplx<T> past,
+                     cplx<T>* t) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < H; ++r) t[r] = past;
         if (__builtin_amdgcn_ballot_w64(zb < len)) {
             cplx<T> q[H];
 #pragma unroll
-            for (int r = 0; r < H; ++r) q[r] = rows_[zb + r < len ? (size_t)(off + zb + r) * ny + e : 0];
+            for (int r = 0; r < H; ++r) {
+                const size_t at = zb + r < len ? (size_t)(off + zb + r) * ny + e : 0;
+                q[r] = cvt<T>(rows_[at]);
+                if constexpr (LOW) q[r] = cadd(q[r], cvt<T>(low[at]));
+            }
 #pragma unroll
             for (int r = 0; r < H; ++r) {
                 const bool tab = zb + r < len;
@@ -618,7 +638,7 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
     auto pivots = [&](int z0) __attribute__((always_inline)) {
         const int zb = z0 + seg * L;
 #pragma unroll
-        for (int h = 0; h < L; h += H) table(a.wrows, roff, elen, zb + h, winf, w + h);
+        for (int h = 0; h < L; h += H) table(a.wrows, a.wrowsl, roff, elen, zb + h, winf, w + h);
 #pragma unroll
         for (int r = 0; r < L; ++r) {
             const int z = zb + r;
@@ -683,14 +703,14 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
         pivots(z0);
 #pragma unroll
         for (int r = 0; r < L; ++r) {
-            y[r] = cscale(y[r], a.scale);
+            y[r] = cscale(y[r], (T)a.scale);
             if (sing && z0 + seg * L + r < nz) y[r].x -= proj;
         }
         if constexpr (PERZ) {
 #pragma unroll
             for (int h = 0; h < L; h += H) {
                 cplx<T> al[H];
-                table(a.arows, aoff, alen, z0 + seg * L + h, zero, al);
+                table(a.arows, nullptr, aoff, alen, z0 + seg * L + h, zero, al);
 #pragma unroll
                 for (int r = 0; r < H; ++r) {
                     y0.x += al[r].x * y[h + r].x;
@@ -715,7 +735,7 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
 #pragma unroll
             for (int r = 0; r < L; ++r) {
                 const int z = z0 + seg * L + r;
-                if (on && z < nz) col[(size_t)z * zs] = y[r];
+                if (on && z < nz) col[(size_t)z * zs] = cvt<Ts>(y[r]);
             }
         }
     }
@@ -753,7 +773,7 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
 #pragma unroll
             for (int h = 0; h < L; h += H) {
                 cplx<T> q[H];
-                table(a.qrows, qoff, qlen, z0 + seg * L + h, zero, q);
+                table(a.qrows, nullptr, qoff, qlen, z0 + seg * L + h, zero, q);
 #pragma unroll
                 for (int r = 0; r < H; ++r) {
                     if (z0 + seg * L + h + r == nz - 1) q[r] = qlast;
@@ -775,7 +795,7 @@ __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<T>* __restrict__ S,
             p = mk<T>(-w[r].x * p.x, -w[r].y * p.y);
             const cplx<T> u = cadd(y[r], p);
             if (on && z < nz) {
-                col[(size_t)z * zs] = u;
+                col[(size_t)z * zs] = cvt<Ts>(u);
                 csum += (double)u.x;
             }
         }
@@ -887,13 +907,13 @@ template <typename T> hipError_t launch_ylines(cplx<T>* S, const LineArgs<T>& a,
     return run_ylines<T, 256>(S, a, inverse, s);
 }
 
-template <typename T, int L, bool PERZ, bool ONE>
-static hipError_t run_zscan(cplx<T>* S, const MidArgs<T>& a, const ScanArgs& g, int batch, hipStream_t s) {
+template <typename Ts, typename T, int L, bool PERZ, bool ONE>
+static hipError_t run_zscan(cplx<Ts>* S, const MidArgs<Ts>& a, const ScanArgs& g, int batch, hipStream_t s) {
     const int ct = 1 << g.lct;
     const int nth = (ct * g.segs + 63) / 64 * 64;
     const size_t lds = (size_t)(nth / 64) * (2 * ct * sizeof(cplx<T>) + sizeof(double));
     const int tiles = (a.slots * a.ny + ct - 1) / ct;
-    hipLaunchKernelGGL((k_zscan<T, L, PERZ, ONE>), dim3(tiles, batch), dim3(nth), lds, s, S, a, g);
+    hipLaunchKernelGGL((k_zscan<Ts, T, L, PERZ, ONE>), dim3(tiles, batch), dim3(nth), lds, s, S, a, g);
     return hipGetLastError();
 }
 
@@ -913,14 +933,21 @@ template <typename T> hipError_t launch_zscan(cplx<T>* S, const MidArgs<T>& a, S
     if (g.chunks > 1) P = pmax;
     g.segs = P;
     if (a.zper) {
-        if (L == 8 && g.chunks == 1) return run_zscan<T, 8, true, true>(S, a, g, batch, s);
+        if (L == 8 && g.chunks == 1) return run_zscan<T, T, 8, true, true>(S, a, g, batch, s);
         constexpr int LP = sizeof(T) == 8 ? 8 : 16;
-        if (g.chunks == 1) return run_zscan<T, LP, true, true>(S, a, g, batch, s);
-        return run_zscan<T, LP, true, false>(S, a, g, batch, s);
+        if (g.chunks == 1) return run_zscan<T, T, LP, true, true>(S, a, g, batch, s);
+        return run_zscan<T, T, LP, true, false>(S, a, g, batch, s);
     }
-    if (L == 8) return run_zscan<T, 8, false, true>(S, a, g, batch, s);
-    if (g.chunks == 1) return run_zscan<T, 16, false, true>(S, a, g, batch, s);
-    return run_zscan<T, 16, false, false>(S, a, g, batch, s);
+    if constexpr (sizeof(T) == 4) {
+        if (a.wrowsl) {
+            if (L == 8) return run_zscan<T, double, 8, false, true>(S, a, g, batch, s);
+            if (g.chunks == 1) return run_zscan<T, double, 16, false, true>(S, a, g, batch, s);
+            return run_zscan<T, double, 16, false, false>(S, a, g, batch, s);
+        }
+    }
+    if (L == 8) return run_zscan<T, T, 8, false, true>(S, a, g, batch, s);
+    if (g.chunks == 1) return run_zscan<T, T, 16, false, true>(S, a, g, batch, s);
+    return run_zscan<T, T, 16, false, false>(S, a, g, batch, s);
 }
 
 #define PP_PLANE_INST(T)                                                                                           \

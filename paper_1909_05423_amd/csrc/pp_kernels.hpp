@@ -132,6 +132,7 @@ template <typename T> struct MidArgs {
     const cplx<T>* wrows;    // [row][ny] (w_re, w_im) reciprocal pivots
     const cplx<T>* winf;     // [slot][ny] converged reciprocal pivot
     const cplx<T>* wlast;    // [slot][ny] reciprocal pivot of the last row
+    const cplx<T>*wrowsl, *winfl, *wlastl;   // what rounding took off them (float z-systems in one pass), or null
     // split march (non-periodic z): rows 0 .. zsplit-1 eliminated downward from
     // z = 0 with the pivots above, rows zsplit .. nz-1 upward from z = nz-1 with
     // the pivots of the reversed system (row nz-1-j at table row j); the two

@@ -37,6 +37,18 @@ def test_records_of_many_batch_entries_are_bounded_by_the_grid():
     assert two < 2.1 * one
 
 
+@pytest.mark.parametrize("nz", [2270, 2280, 2290])
+def test_low_parts_of_pivots_do_not_take_a_plan_past_the_fixed_workspace(nz):
+    # (within 2 MB of it; the low parts of the pivots of these columns take 3 to 5)
+    lib = _lib.load()
+    p = ctypes.c_void_p()
+    assert lib.pp_plan_create(96, 128, nz, b"DDDDDD", (ctypes.c_double * 3)(1.0, 1.0, 0.2), _lib.PP_F32, 1,
+                              ctypes.byref(p)) == 0
+    n = lib.pp_plan_workspace_bytes(p)
+    lib.pp_plan_destroy(p)
+    assert n <= _lib.NOALLOC_SCRATCH_BYTES
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_noalloc_solve_of_long_rows_and_a_batch(dtype):
