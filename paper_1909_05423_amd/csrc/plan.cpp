@@ -1099,9 +1099,21 @@ template <typename T> pp::PlaneArgs<T> make_planeargs(pp_plan p, unsigned char* 
 // over segments is (2047 x 32 x 96 PP PP DN: 4.4e-7 split, 1.7e-6 in one pass).
 // Other float plans that the march would split take their pivots in two floats
 // and the recurrences in double (k_zscan).
+// Few planes leave most of the chip idle for as long as a workgroup takes over one,
+// while the x kernels spread their rows and a march over few planes is short.
+// Measured on 2568 shapes of 2 to 47 planes: the march was the faster below 12
+// planes of more than 8192 values (march and planes: f32 2 x 162 x 192 42 and 59
+// us, 4 x 128 x 192 x 2 42 and 47, f64 3 x 96 x 162 x 2 39 and 45), and below 32 of
+// 4096 or more where its x kernels are the exact-count ones of 256 (f32 16 x 96 x
+// 256 28 and 43, 30 x 96 x 256 36 and 44, f64 3 x 64 x 256 x 3 36 and 44); elsewhere
+// the planes, but for one of 2334 by more than 4%.
+bool few_planes(pp_plan p) {
+    const int values = p->nx * p->ny;
+    return pp::x_exact(p->nx, p->ny, p->ty) ? p->nz < 32 && values >= 4096 : p->nz < 12 && values > 8192;
+}
 bool use_planes(pp_plan p) {
     return p->plane_ok && p->zsolver == 0 && p->zsplit_mode == PP_ZSPLIT_AUTO &&
-           (p->dtype == PP_F64 || p->split_gmax <= kSplitGMax);
+           (p->dtype == PP_F64 || p->split_gmax <= kSplitGMax) && !few_planes(p);
 }
 
 // The z stage in three passes (y transforms by themselves around the z-systems
