@@ -1125,13 +1125,17 @@ bool use_planes(pp_plan p) {
 // 200 x 384 x 256 337 and 279 us (49,152 pairs), 256 x 256 x 384 362 and 370
 // (49,152), 256^3 338 and 246 (32,768); f32 256 x 256 x 384 285 and 201
 // (49,152), 200 x 384 x 384 310 and 290 (73,728), 512 x 256 x 512 607 and 692
-// (65,536); on lines of 512, whose march keeps stages in registers, f64
-// 200 x 512 x 128 253 and 216 (32,768), 200 x 512 x 192 254 and 297.
+// (65,536); lines of 512, f64 and f32, periodic and DCT, 0.62-0.89 of the march
+// from 200 planes on at 24,576 to 41,472 pairs.  Few planes make the march short:
+// below 20 planes, or 900 pairs a plane, it is the passes that take longer (f32 9 x
+// 128 x 256 x 2 38 and 56 us, f64 16 x 384 x 54 x 4 92 and 111, 25 x 192 x 384 68
+// and 73; on lines of 512 with 32 planes 1.02 at 24,576 pairs and 1.19 at 55,296,
+// with 64 planes 0.88 and 1.01).
 template <typename T> bool use_lines(pp_plan p, const pp::MidArgs<T>& ma) {
     const long long pairs = (long long)p->slots * p->batch * p->ny;
-    const long long most = p->ny == 512 ? 32768 : (sizeof(T) == 8 ? 45056 : 61440);
+    const long long most = std::min<long long>(sizeof(T) == 8 ? 45056 : 61440, 900LL * p->nz);
     return p->lines_ok && p->zsolver == 0 && p->zsplit_mode == PP_ZSPLIT_AUTO && ma.zsplit == 0 && ma.zsegs == 0 &&
-           pairs <= most;
+           p->nz >= 20 && pairs <= most;
 }
 
 template <typename T>

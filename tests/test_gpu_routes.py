@@ -2,7 +2,9 @@
 they agree with the march of one workgroup per column there.
 
 The plane kernels reduce the source's sums in their z kernel, so a solve by them
-has no launch in the group of reductions (pp_plan_kernel_times)."""
+has no launch in the group of reductions (pp_plan_kernel_times); the separate y
+transforms around the z-systems round differently from the march, so equal bits
+mean that the march ran."""
 
 import ctypes
 
@@ -56,4 +58,24 @@ def test_planes(dtype, shape, batch, planes, bc, faces):
     u, took = _run(shape, bc, dtype, batch, "auto", faces)
     v, march = _run(shape, bc, dtype, batch, "off", faces)
     assert took == planes and not march
+    assert _close(u, v, dtype)
+
+
+# (shape, batch, the y transforms run by themselves): 20 planes, 900 pairs a plane, the
+# most pairs; lines of 512 as others
+LINES = [("f32", (9, 128, 256), 2, False), ("f32", (19, 18, 288), 1, False), ("f32", (20, 18, 288), 1, True),
+         ("f64", (25, 192, 384), 1, False), ("f64", (48, 192, 384), 1, True), ("f64", (200, 512, 144), 1, True),
+         ("f32", (70, 512, 216), 1, True), ("f64", (70, 512, 192), 1, False), ("f32", (32, 512, 128), 1, False),
+         ("f32", (80, 256, 486), 1, False)]
+
+
+@pytest.mark.parametrize("bc", ["NNPPPP", "PPNNPP"])
+@pytest.mark.parametrize("dtype,shape,batch,lines", LINES)
+def test_separate_y_transforms(dtype, shape, batch, lines, bc):
+    import torch
+    from gpu_util import banner
+    banner(f"route lines {dtype} {shape} x {batch} {bc}")
+    u, _ = _run(shape, bc, dtype, batch, "auto")
+    v, _ = _run(shape, bc, dtype, batch, "off")
+    assert torch.equal(u, v) != lines
     assert _close(u, v, dtype)
