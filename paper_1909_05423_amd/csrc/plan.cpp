@@ -833,17 +833,9 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 // one contiguous stretch of the array rather than one line in each of a few
 // hundred columns a power of two apart; the x kernels write and read whole
 // z planes either way.
-#ifndef PP_SPECTRAL_ZMAJOR
-#define PP_SPECTRAL_ZMAJOR 1
-#endif
 void spectral_strides(pp_plan p, long* sstride, long* zstride) {
-    if (PP_SPECTRAL_ZMAJOR) {
-        *sstride = p->ny;
-        *zstride = (long)p->slots * p->ny;
-    } else {
-        *sstride = (long)p->nz * p->ny;
-        *zstride = p->ny;
-    }
+    *sstride = p->ny;
+    *zstride = (long)p->slots * p->ny;
 }
 
 // Refined solve: the spectral slots of the smallest x wavenumbers, whose z
