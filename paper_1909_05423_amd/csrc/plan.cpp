@@ -44,7 +44,7 @@ struct Tables {
     size_t t_rrowoff = 0, t_relen = 0, t_rrows = 0, t_rholast = 0, t_segk = 0;
     // periodic z (Sherman-Morrison)
     size_t t_aelen = 0, t_qelen = 0;
-    size_t t_aoff = 0, t_alen = 0, t_arows = 0, t_qoff = 0, t_qlen = 0, t_qrows = 0, t_qlast = 0, t_invden = 0,
+    size_t t_aoff = 0, t_arows = 0, t_qoff = 0, t_qrows = 0, t_qlast = 0, t_invden = 0,
            t_invgam = 0;
     size_t table_rows = 0;
 };
@@ -778,7 +778,7 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
     }
     if (p->bz0 != pp::BC_P) return;
     // periodic z: Sherman-Morrison rows (alpha, qp) per slot, and per-entry scalars
-    auto emit_rows = [&](std::vector<T> Line<T>::*vec, size_t* t_off, size_t* t_len, size_t* t_rows, size_t* t_elen) {
+    auto emit_rows = [&](std::vector<T> Line<T>::*vec, size_t* t_off, size_t* t_rows, size_t* t_elen) {
         std::vector<int> off(slots), len(slots), elen((size_t)slots * ny);
         for (int m = 0; m < slots; ++m)
             for (int e = 0; e < ny; ++e)
@@ -796,8 +796,6 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
         }
         *t_off = em.put(sizeof(int) * slots);
         std::memcpy(tb.blob.data() + *t_off, off.data(), sizeof(int) * slots);
-        *t_len = em.put(sizeof(int) * slots);
-        std::memcpy(tb.blob.data() + *t_len, len.data(), sizeof(int) * slots);
         *t_rows = em.put(sizeof(T) * 2 * std::max<size_t>(nrows, 1) * ny);
         T* rr = reinterpret_cast<T*>(tb.blob.data() + *t_rows);
         for (int m = 0; m < slots; ++m)
@@ -808,8 +806,8 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
                         rr[((size_t)(off[m] + z) * ny + e) * 2 + part] = (z < (int)v.size()) ? v[z] : T(0);
                     }
     };
-    emit_rows(&Line<T>::alpha, &tb.t_aoff, &tb.t_alen, &tb.t_arows, &tb.t_aelen);
-    emit_rows(&Line<T>::qp, &tb.t_qoff, &tb.t_qlen, &tb.t_qrows, &tb.t_qelen);
+    emit_rows(&Line<T>::alpha, &tb.t_aoff, &tb.t_arows, &tb.t_aelen);
+    emit_rows(&Line<T>::qp, &tb.t_qoff, &tb.t_qrows, &tb.t_qelen);
     auto emit_scalar = [&](T Line<T>::*field, size_t* t) {
         *t = em.put(sizeof(T) * 2 * (size_t)slots * ny);
         T* v = reinterpret_cast<T*>(tb.blob.data() + *t);
@@ -1004,12 +1002,10 @@ pp::MidArgs<T> make_midargs(pp_plan p, unsigned char* ws, bool project, bool dem
     a.zper = (p->bz0 == pp::BC_P) ? 1 : 0;
     if (a.zper) {
         a.aoff = reinterpret_cast<const int*>(t + tb.t_aoff);
-        a.alen = reinterpret_cast<const int*>(t + tb.t_alen);
         a.aelen = reinterpret_cast<const int*>(t + tb.t_aelen);
         a.qelen = reinterpret_cast<const int*>(t + tb.t_qelen);
         a.arows = reinterpret_cast<const cplx<T>*>(t + tb.t_arows);
         a.qoff = reinterpret_cast<const int*>(t + tb.t_qoff);
-        a.qlen = reinterpret_cast<const int*>(t + tb.t_qlen);
         a.qrows = reinterpret_cast<const cplx<T>*>(t + tb.t_qrows);
         a.qlast = reinterpret_cast<const cplx<T>*>(t + tb.t_qlast);
         a.inv_den = reinterpret_cast<const cplx<T>*>(t + tb.t_invden);
@@ -1507,16 +1503,14 @@ pp_status pp_plan_create(int nx, int ny, int nz, const char bc[6], const double 
         // the inverse gathers slots * lines (slot, row pair) values, kXVals/2 per thread
         while (lines > 1 && (size_t)((nx + 1) / 2) * lines > (size_t)pp::xdir_threads(nx) * (pp::kXVals / 2)) --lines;
         // LDS: the lines plus the twiddle tables (the second, of the DCT, with
-        // Neumann or Dirichlet rows); fewer lines to keep two workgroups per CU
-        // (the refined solve's forward x transform works in double).  Lines
-        // shared by wavefronts bring enough of them in one workgroup and keep
-        // four lines (eight rows: whole 128-byte lines of double spectra) where
-        // the LDS allows.
+        // Neumann or Dirichlet rows); the refined solve's forward x transform works
+        // in double.  Rows up to 512 take at most 54 KB of it; of longer ones, which
+        // bring enough wavefronts in one workgroup, four lines (eight rows: whole
+        // 128-byte lines of double spectra) where they fit.
         const size_t xelem = (dtype == PP_F32) ? sizeof(cplx<float>) : sizeof(cplx<double>);
         const size_t tables = p->bx == pp::BC_P ? 1 : 2;
         auto xlds = [&](int l) { return ((size_t)l * pp::padded_len(nx) + tables * (size_t)nx) * xelem; };
-        const size_t target = lw > 64 ? (size_t)pp::kXLdsMax : (size_t)pp::kXLdsBytes;
-        while (lines > 1 && xlds(lines) > target) --lines;
+        while (lines > 1 && xlds(lines) > (size_t)pp::kXLdsMax) --lines;
         if (xlds(lines) > (size_t)pp::kXLdsMax) lines = 0;
     }
     if (lines < 1) {

@@ -430,14 +430,12 @@ __global__ __launch_bounds__(NTH) void k_plane_inv(const cplx<T>* __restrict__ S
 // ---------------------------------------------------------------------------
 // The y transforms of spectral lines by themselves, in place (grids whose planes
 // do not fit in LDS and whose columns are too few for the z march): a workgroup
-// takes a group of whole lines (b, z, slot), kLineVals values per thread.
+// takes a group of whole lines (b, z, slot), kPlaneVals values per thread.
 // ---------------------------------------------------------------------------
-template <typename T> constexpr int kLineVals = sizeof(T) == 8 ? 8 : 16;
-
 template <typename T, int NTH, bool INV>
 __global__ __launch_bounds__(NTH) void k_ylines(cplx<T>* __restrict__ S, LineArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int V = kLineVals<T>;
+    constexpr int V = kPlaneVals<T>;
     const int ny = a.ny, ld = a.ld, tid = threadIdx.x;
     const size_t first = (size_t)blockIdx.x * a.group;
     const int nl = (int)(a.nlines - first < (size_t)a.group ? a.nlines - first : (size_t)a.group);
@@ -891,7 +889,7 @@ hipError_t launch_plane_inv(const cplx<T>* S, T* u, const PlaneArgs<T>& a, int b
 template <typename T, int NTH>
 static hipError_t run_ylines(cplx<T>* S, LineArgs<T> a, bool inverse, hipStream_t s) {
     a.ld = a.ny | 1;
-    a.group = kLineVals<T> * NTH / a.ny;
+    a.group = kPlaneVals<T> * NTH / a.ny;
     if ((size_t)a.group > a.nlines) a.group = (int)a.nlines;
     const size_t lds = ((size_t)a.group * a.ld + (size_t)(a.by != BC_P ? 2 : 1) * a.ny) * sizeof(cplx<T>);
     const dim3 grid((unsigned)((a.nlines + a.group - 1) / a.group));

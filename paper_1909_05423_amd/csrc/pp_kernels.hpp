@@ -25,8 +25,7 @@ constexpr int kXGroups = 4;
 constexpr int xdir_waves(int nx) { return nx <= 512 ? 1 : (nx <= 1024 ? 2 : 4); }
 constexpr int xdir_threads(int nx) { return 64 * kXGroups * xdir_waves(nx); }
 constexpr int kXGridMax = 1024;                // largest grid of an x kernel: four workgroups for each of 256 CUs
-constexpr int kXLdsBytes = 96 * 1024;          // x-kernel LDS target (lines + twiddle tables), two workgroups per CU
-constexpr int kXLdsMax = 160 * 1024 - 1024;    // x-kernel LDS ceiling (one workgroup per CU)
+constexpr int kXLdsMax = 160 * 1024 - 1024;    // most LDS of a workgroup (lines + twiddle tables)
 // Radix-9 stages in the x kernels of any length: in float, and in double where
 // the workgroup's size sets the registers anyway.  Elsewhere in double they take
 // 135 registers instead of 125 and a workgroup per CU with them (x forward of 128
@@ -166,7 +165,7 @@ template <typename T> struct MidArgs {
     // alpha = first row of the inverse of the split matrix and of the
     // forward-eliminated rank-one vector; per entry its last value, 1/den, 1/gamma
     int zper;
-    const int *aoff, *alen, *qoff, *qlen;
+    const int *aoff, *qoff;
     const int *aelen, *qelen;   // per (slot, entry): rows of alpha / qp before they are zero
     const cplx<T> *arows, *qrows, *qlast, *inv_den, *inv_gamma;
     // z solver: 0 = fused Thomas march, 1 = parallel cyclic reduction, 2 = CR-P (separate y passes)
@@ -325,7 +324,7 @@ hipError_t scratch_buffer(void** ptr);
 
 // Scalar block layout (doubles) used by the refinement loop.
 enum Scalar : int {
-    SC_MAXF = 0,      // max |f|
+    SC_MAXF = 0,      // max |f| (the plane kernels: |mean f| of the first batch entry, as finite as its f)
     SC_MAXD = 1,      // max |correction| of the last update
     SC_MAXU = 2,      // max |u| after the last update
     SC_REL = 3,       // SC_MAXD / SC_MAXU

@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <new>
 #include <set>
 #include <tuple>
 #include <type_traits>
@@ -876,7 +877,11 @@ template <auto K> static hipError_t x_resident(int threads, size_t lds, int* out
     int n = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, lds);
     if (e != hipSuccess) return e;
-    *out = known[{dev, lds}] = n < 1 ? 1 : n;
+    *out = n < 1 ? 1 : n;
+    try {
+        known[{dev, lds}] = *out;
+    } catch (const std::bad_alloc&) {   // not kept: asked again by the next launch
+    }
     return hipSuccess;
 }
 
@@ -903,9 +908,7 @@ template <typename A, typename B, typename T> static bool x_far(const XArgs<T>& 
     return points * (sizeof(A) + sizeof(B)) > ((size_t)256 << 20);
 }
 
-
 int x_blocks(int ny, int ty, int nz, int batch) { return ((ny + ty - 1) / ty) * nz * batch; }
-
 
 template <typename T, typename Tin, typename Ts, int WPL, int RMAX, bool FACES, bool RES = false>
 static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, const XArgs<T>& a, int batch,
@@ -915,24 +918,23 @@ static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, 
     int resident = 1;
     if constexpr (WPL <= 2) {
         if (a.nx == 64 * WPL * RMAX && x_exact(a.nx, a.ny, a.ty)) {
-            const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>(threads, x_lds_bytes(a), &resident);
+            const hipError_t le =
+                x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
             const int grid = x_grid(nb, false, resident, sizeof(T) == 8 && x_far<Tin, Ts>(a, batch));
             *records = grid * kXGroups;
-            hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>),
-                               dim3(grid), dim3(threads), x_lds_bytes(a), s, f, S, partial, a,
-                               nb, fa);
+            hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>), dim3(grid), dim3(threads),
+                               x_lds_bytes(a), s, f, S, partial, a, nb, fa);
             return hipGetLastError();
         }
     }
-    {
-        const hipError_t le = x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>>(threads, x_lds_bytes(a), &resident);
-            if (le != hipSuccess) return le;
-            const int grid = x_grid(nb, false, resident, false);
-            *records = grid * kXGroups;
-        hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>), dim3(grid),
-                           dim3(threads), x_lds_bytes(a), s, f, S, partial, a, nb, fa);
-    }
+    const hipError_t le =
+        x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>>(threads, x_lds_bytes(a), &resident);
+    if (le != hipSuccess) return le;
+    const int grid = x_grid(nb, false, resident, false);
+    *records = grid * kXGroups;
+    hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, false, FACES, RES>), dim3(grid), dim3(threads), x_lds_bytes(a), s,
+                       f, S, partial, a, nb, fa);
     return hipGetLastError();
 }
 
@@ -982,25 +984,23 @@ static hipError_t launch_xinv_shape(const cplx<T>* S, Tout* u, const Tp* uprev, 
     int resident = 1;
     if constexpr (WPL <= 2) {
         if (a.nx == 64 * WPL * RMAX && x_exact(a.nx, a.ny, a.ty)) {
-            const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>(threads, x_lds_bytes(a), &resident);
+            const hipError_t le =
+                x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
-            const int grid = x_grid(nb, sizeof(T) == 4, resident, (sizeof(Tout) == 8 || MODE != XINV_STORE) && x_far<T, Tout>(a, batch));
+            const bool two = (sizeof(Tout) == 8 || MODE != XINV_STORE) && x_far<T, Tout>(a, batch);
+            const int grid = x_grid(nb, sizeof(T) == 4, resident, two);
             if (records) *records = grid * kXGroups;
-            hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>),
-                               dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u,
-                               uprev, a, shift, scalars, gauge_region, partial, nb);
+            hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, true>), dim3(grid), dim3(threads), x_lds_bytes(a),
+                               s, S, u, uprev, a, shift, scalars, gauge_region, partial, nb);
             return hipGetLastError();
         }
     }
-    {
-        const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>>(threads, x_lds_bytes(a), &resident);
-            if (le != hipSuccess) return le;
-            const int grid = x_grid(nb, sizeof(T) == 4, resident, false);
-            if (records) *records = grid * kXGroups;
-        hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>),
-                           dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u, uprev,
-                           a, shift, scalars, gauge_region, partial, nb);
-    }
+    const hipError_t le = x_resident<k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>>(threads, x_lds_bytes(a), &resident);
+    if (le != hipSuccess) return le;
+    const int grid = x_grid(nb, sizeof(T) == 4, resident, false);
+    if (records) *records = grid * kXGroups;
+    hipLaunchKernelGGL((k_xinv<T, Tout, Tp, WPL, MODE, RMAX, false>), dim3(grid), dim3(threads), x_lds_bytes(a), s, S, u,
+                       uprev, a, shift, scalars, gauge_region, partial, nb);
     return hipGetLastError();
 }
 
