@@ -262,10 +262,14 @@ template <typename T> struct Line {
     std::vector<T> body;
     T winf = 0, wlast = 0;
     int tail = 0;
-    std::vector<T> bodyl;           // what rounding to T took off the pivots (not periodic z)
-    T winfl = 0, wlastl = 0;
     std::vector<T> alpha, qp;       // periodic z only
     T qlast = 0, inv_den = 0, inv_gamma = 0;
+};
+
+// What rounding to T took off a line's pivots.
+template <typename T> struct LineLow {
+    std::vector<T> body;
+    T winf = 0, wlast = 0;
 };
 
 template <typename T> static int significant_prefix(const std::vector<double>& v) {
@@ -309,7 +313,7 @@ template <typename T> void periodic_extras(double bmid, int nz, const std::vecto
 // instead of 3e-9 at 2048 rows, lambda h^2 = 1e-5).
 template <typename T>
 void pivots(double lam, int nz, double hz, int bz0, int bz1, bool pinned, Line<T>* out, int krow = -1,
-            double* wk = nullptr, bool low = false) {
+            double* wk = nullptr, LineLow<T>* low = nullptr) {
     const double bmid = -2.0 + hz * hz * lam;
     out->alpha.clear();
     out->qp.clear();
@@ -338,7 +342,7 @@ void pivots(double lam, int nz, double hz, int bz0, int bz1, bool pinned, Line<T
     if (nz == 1) {
         const double only = pinned ? 0.0 : 1.0 / (bmid + d0 + d1);
         out->wlast = (T)only;
-        out->wlastl = (T)(only - (double)out->wlast);
+        if (low) low->wlast = (T)(only - (double)out->wlast);
         out->winf = 0;
         out->tail = 0;
         return;
@@ -357,18 +361,18 @@ void pivots(double lam, int nz, double hz, int bz0, int bz1, bool pinned, Line<T
     if (krow >= 0 && wk) *wk = seq[std::min((size_t)krow, seq.size() - 1)];
     const double wl = 1.0 / ((bmid + d1) - wend);
     out->wlast = (T)wl;
-    out->wlastl = (T)(wl - (double)out->wlast);
     out->winf = (T)wend;
-    out->winfl = (T)(wend - (double)out->winf);
     int L = (int)seq.size();
     while (L > 0 && (T)seq[L - 1] == out->winf && (!low || std::fabs(seq[L - 1] - wend) <= 0x1p-30 * std::fabs(wend)))
         --L;
     out->tail = L;
     out->body.resize(L);
-    out->bodyl.resize(L);
-    for (int i = 0; i < L; ++i) {
-        out->body[i] = (T)seq[i];
-        out->bodyl[i] = (T)(seq[i] - (double)out->body[i]);
+    for (int i = 0; i < L; ++i) out->body[i] = (T)seq[i];
+    if (low) {
+        low->wlast = (T)(wl - (double)out->wlast);
+        low->winf = (T)(wend - (double)out->winf);
+        low->body.resize(L);
+        for (int i = 0; i < L; ++i) low->body[i] = (T)(seq[i] - (double)out->body[i]);
     }
 }
 
@@ -533,6 +537,7 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
     std::vector<int> rowoff(slots), lmax(slots), elen((size_t)slots * ny);
     std::vector<T> winf((size_t)slots * ny * 2), wlast((size_t)slots * ny * 2);
     std::vector<std::vector<Line<T>>> lines(slots);
+    std::vector<std::vector<LineLow<T>>> lows(p->pivots_low ? slots : 0);
     // split march: the lower half's lines and, per (slot, entry, part), the
     // meeting rows' pivots w (row zsplit-1, top-down), v (row zsplit,
     // bottom-up) and 1 / (1 - v w), all from double
@@ -546,6 +551,7 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
         const bool pairslot = (p->bx != pp::BC_P) || (m == 0);
         const bool sep = (p->by == pp::BC_P) && pairslot;
         lines[m].resize((size_t)ny * 2);
+        if (p->pivots_low) lows[m].resize((size_t)ny * 2);
         int lm = 0;
         for (int e = 0; e < ny; ++e) {
             for (int part = 0; part < 2; ++part) {
@@ -567,7 +573,7 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
                 } else {
                     const bool pinned = p->singular && m == 0 && e == 0 && part == 0;
                     pivots<T>(lamx[kx] + lamy[ky], nz, p->h[2], p->bz0, p->bz1, pinned, &ln, ks - 1, &wk,
-                              p->pivots_low);
+                              p->pivots_low ? &lows[m][(size_t)e * 2 + part] : nullptr);
                 }
                 if (nseg > 0) {
                     if (slines[m].empty()) slines[m].resize((size_t)ny * 2);
@@ -630,8 +636,8 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
         std::vector<T> low((size_t)slots * ny * 2), lastl(low.size());
         for (int m = 0; m < slots; ++m)
             for (int e = 0; e < 2 * ny; ++e) {
-                low[(size_t)m * ny * 2 + e] = lines[m][e].winfl;
-                lastl[(size_t)m * ny * 2 + e] = lines[m][e].wlastl;
+                low[(size_t)m * ny * 2 + e] = lows[m][e].winf;
+                lastl[(size_t)m * ny * 2 + e] = lows[m][e].wlast;
             }
         tb.t_winfl = em.put(sizeof(T) * low.size());
         std::memcpy(tb.blob.data() + tb.t_winfl, low.data(), sizeof(T) * low.size());
@@ -642,8 +648,8 @@ template <typename T> void build_tables(pp_plan p, Tables& tb) {
         for (int m = 0; m < slots; ++m)
             for (int z = 0; z < lmax[m]; ++z)
                 for (int e = 0; e < 2 * ny; ++e) {
-                    const Line<T>& ln = lines[m][e];
-                    wl[(size_t)(rowoff[m] + z) * ny * 2 + e] = (z < ln.tail) ? ln.bodyl[z] : ln.winfl;
+                    const LineLow<T>& ll = lows[m][e];
+                    wl[(size_t)(rowoff[m] + z) * ny * 2 + e] = (z < (int)ll.body.size()) ? ll.body[z] : ll.winf;
                 }
     }
     if (ks > 0) {

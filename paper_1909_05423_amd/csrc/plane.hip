@@ -525,9 +525,10 @@ __global__ __launch_bounds__(NTH) void k_ylines(cplx<T>* __restrict__ S, LineArg
 // pivots, which is the same in every row past their table, further than the
 // pieces of a split or segmented march do.  There the pivots are in two floats
 // (MidArgs::wrowsl) and the recurrences in double, which leaves the rounding of
-// the spectra themselves (rms error from the f64 solve, one float recurrence, the
-// split march and this: 1000 x 128 x 64 DDDDDN x 16 1.2e-6, 5.2e-7, 4.6e-7; 2048
-// x 32 x 128 x 6 2.0e-6, 8.1e-7, 5.5e-7; 64 x 64 x 64 x 16 gradient 104 -> 111 us).
+// the spectra themselves (rms error from the f64 solve of one float recurrence,
+// of the split march and of this: 1000 x 128 x 64 DDDDDN x 16 1.2e-6, 5.3e-7 and
+// 2.1e-7; 2048 x 32 x 128 x 6 2.0e-6, 8.1e-7 and 1.9e-7; 64 x 64 x 64 x 16 gradient
+// 104 us either way).
 template <typename Ts, typename T, int L, bool PERZ, bool ONE>
 __global__ __launch_bounds__(kScanThreads) void k_zscan(cplx<Ts>* __restrict__ S, MidArgs<Ts> a, ScanArgs g) {
     constexpr bool LOW = !std::is_same_v<Ts, T>;
