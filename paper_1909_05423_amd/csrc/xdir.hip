@@ -183,6 +183,10 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
     // nor with the split store, which spilled with it)
     constexpr bool R512 = FULL && WPL == 1 && RMAX == 8 && sizeof(T) == 8 && !RES && !SPLIT;
     const bool reg512 = R512 && a.bx == BC_P;
+    // float rows of 512: stages by the run-time plan (186 registers), which past
+    // the last-level cache is the faster form: 512^3 244 us against 260 with stages
+    // known to the compiler (156 registers); 97 and 88 on 512 x 512 x 200
+    constexpr bool EXACT = FULL && !(WPL == 1 && RMAX == 8 && sizeof(T) == 4);
 
     // register r: line j = wave + NG * (r / epl), column n = lane + LW * (r % epl)
     Tin ra[RMAX], rb[RMAX];
@@ -504,7 +508,8 @@ __global__ __launch_bounds__(64 * kXGroups * WPL) __attribute__((amdgpu_waves_pe
             }
         } else if (FULL || WPL > 1) {
             line_sync<LW>();
-            if constexpr (FULL) wfft_exact<LW * RMAX, false, T, true, LW>(lds + wave * ldl, twl, lane);
+            if constexpr (EXACT) wfft_exact<LW * RMAX, false, T, true, LW>(lds + wave * ldl, twl, lane);
+            else if constexpr (FULL) wfft<RMAX, false, T>(lds + wave * ldl, a.fx, twl, lane);
             else wfft<RMAX, false, T, true, LW, NINE>(lds + wave * ldl, a.fx, twl, lane, wave < nlines);
         } else {
             for (int j = wave; j < nlines; j += NG) {
@@ -891,11 +896,12 @@ template <auto K> static hipError_t x_resident(int threads, size_t lds, int* out
 // second set starts as the first ones end, out of step with one another.
 // Measured against two per CU throughout (x forward / inverse): 553 x 256 x 216
 // f64 200 / 213 -> 154 / 171 us, 200 x 288 x 486 f32 147 / 144 -> 107 / 94,
-// 256^3 f64 80 / 80 -> 66 / 64, 512^3 f32 273 / 282 -> 227 / 271.  The
-// exact-count kernels with double data (and the refined solve's) keep two where
-// the source and the spectra are past the 256 MiB last-level cache: they are bound by HBM, and more
-// workgroups only spread their rows (384^3 x 4 inverse 793 -> 866 us with
-// three; 512^3 unchanged).
+// 256^3 f64 80 / 80 -> 66 / 64, 512 x 256 x 400 f32 inverse 107 -> 86.  The
+// exact-count kernels keep two where the source and the spectra are past the
+// 256 MiB last-level cache, but for the float inverse: they are bound by HBM, and
+// more workgroups only spread their rows (f64 384^3 x 4 inverse 793 -> 866 us with
+// three; f32 forward with two / three per CU: 384 x 384 x 800 227 and 264,
+// 256 x 512 x 1600 432 and 491).
 static int x_grid(int nblocks, bool paired, int resident, bool two) {
     const int per = two ? 2 : (resident >= 3 ? (resident < 4 ? resident : 4) : 2 * resident);
     const int work = paired ? (nblocks + 1) / 2 : nblocks;
@@ -921,7 +927,7 @@ static hipError_t launch_xfwd_shape(const Tin* f, cplx<Ts>* S, double* partial, 
             const hipError_t le =
                 x_resident<k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>>(threads, x_lds_bytes(a), &resident);
             if (le != hipSuccess) return le;
-            const int grid = x_grid(nb, false, resident, sizeof(T) == 8 && x_far<Tin, Ts>(a, batch));
+            const int grid = x_grid(nb, false, resident, x_far<Tin, Ts>(a, batch));
             *records = grid * kXGroups;
             hipLaunchKernelGGL((k_xfwd<T, Tin, Ts, WPL, RMAX, true, FACES, RES>), dim3(grid), dim3(threads),
                                x_lds_bytes(a), s, f, S, partial, a, nb, fa);
