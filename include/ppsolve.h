@@ -135,10 +135,13 @@ pp_status pp_plan_set_zsolver(pp_plan p, pp_zsolver solver);
  *                   (lines up to 256; 128 x 128 in double, twice that in
  *                   float; float plans also need the bound on near-singular
  *                   systems below) take whole planes per workgroup and the
- *                   z-systems in one pass instead of the march, and plans
- *                   whose march cannot be split and has few columns the
- *                   z-systems in one pass.  Otherwise split where the columns (x-wavenumber slots times
- *                   batch) are at most 1/2 (PP_F64), 2 (PP_F32) or 4
+ *                   z-systems in one pass instead of the march, except a few
+ *                   large planes (under 12 of more than 8192 values; under 32 of
+ *                   4096 or more on rows of 256 with ny a multiple of 8), and
+ *                   plans of at least 20 planes whose march
+ *                   cannot be split and has few columns the z-systems in one
+ *                   pass.  Otherwise split where the columns (x-wavenumber slots
+ *                   times batch) are at most 1/2 (PP_F64), 2 (PP_F32) or 4
  *                   (PP_F32_REFINED) per compute unit of the device, or, in
  *                   PP_F64 on y lines up to 512 with more columns than
  *                   compute units, where the split's rounds of workgroups
